@@ -75,6 +75,12 @@ def _space(rng, dims):
     return d, points, round(rel * spread, 4)
 
 
+def _resolved(points, eps, k, d):
+    """A bandwidth that k anchors resolve (at most 1.6 times their spacing): with more anchors than the kernel's numerical
+    rank the preconditioner's smallest directions are rounding noise, and no two factorisations agree on them."""
+    return round(min(eps, 2.5 * k ** (-2.0 / d)), 4) if points == "uniform" else eps
+
+
 def draw(rng):
     kind = rng.choices(["product", "predict", "build", "apply", "solve", "grad"], [28, 22, 16, 10, 16, 8])[0]
     prec = rng.choice(["fp64", "fp32", "mixed", "mixed"])
@@ -94,6 +100,7 @@ def draw(rng):
         d, points, eps = _space(rng, [3, 4, 5, 6, 8, 11, 16])
         n = _log_int(rng, 1500, 100000)
         k = _log_int(rng, 50, min(1000, n // 10))
+        eps = _resolved(points, eps, k, d)
         anchors = rng.choice(["sketch", "sketch", "fps", "random"])
         sketch = anchors == "sketch"
         return dict(kind=kind, n=n, d=d, points=points, eps=eps, beta=rng.choice([1e-3, 1e-2]), k=k,
@@ -102,7 +109,8 @@ def draw(rng):
     if kind == "apply":
         d, points, eps = _space(rng, [4, 6, 8, 16])
         n = _log_int(rng, 1500, 100000)
-        return dict(kind=kind, n=n, d=d, points=points, eps=eps, beta=1e-2, k=_log_int(rng, 50, min(1000, n // 10)),
+        k = _log_int(rng, 50, min(1000, n // 10))
+        return dict(kind=kind, n=n, d=d, points=points, eps=_resolved(points, eps, k, d), beta=1e-2, k=k,
                     R=rng.choice([1, 1, 3, 16, 64, 128]), prec=prec)
     # solves: ranks and ridges that converge within some tens of iterations; 32-bit solves stagnate above their
     # tolerance on the smoothest kernels, so they take narrower ones
