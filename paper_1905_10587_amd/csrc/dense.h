@@ -1,7 +1,9 @@
 // Small dense FP64 linear algebra for the preconditioner build (k x k with k up to a few
-// thousand), all column-major: kernel blocks K(A, B), a one-sided Jacobi symmetric EVD, a
-// Cholesky factorisation and a lower-triangular inverse.
+// thousand): kernel blocks K(A, B), a one-sided Jacobi symmetric EVD, a Cholesky factorisation and
+// a lower-triangular inverse.
 #pragma once
+
+#include <algorithm>
 
 #include "krr_internal.h"
 
@@ -16,17 +18,17 @@ void kernel_block_rowmajor(const double* A, int64_t ma, const double* B, int64_t
 // out[a, :] = X[idx[a], :]
 void gather_rows(const double* X, int64_t n, int d, const int64_t* idx, int64_t k, double* out, hipStream_t s);
 
-// Symmetric positive semidefinite EVD by one-sided (Hestenes) Jacobi with a round-robin parallel
-// ordering.  A (k x k, column-major) is overwritten by A V whose columns are orthogonal; V holds
-// the eigenvectors and lam[i] = ||(A V)_i|| the eigenvalues (unsorted).  Returns sweeps used.
-int jacobi_evd(double* A, double* V, double* lam, int k, hipStream_t s, int max_sweeps = 40);
+// Symmetric positive semidefinite EVD by one-sided block Jacobi, on the Cholesky factor of K or on K (jacobi.hip).
+// K (k x k, column-major, not modified): V holds the eigenvectors (column-major) and lam the eigenvalues (unsorted,
+// non-negative).  Returns sweeps used.
+int jacobi_evd(const double* K, double* V, double* lam, int k, bool on_factor, hipStream_t s, int max_sweeps = 40);
 
 // Lower Cholesky factor of the symmetric positive definite A (k x k, column-major, lower part
 // read; A is overwritten).  L receives the factor (upper part zeroed).  Returns 0 on success or
 // (j+1) for the first non-positive or non-finite pivot j.
 int cholesky_lower(double* A, double* L, int k, hipStream_t s);
 
-// X = L^{-1} for lower-triangular L (column-major); X is lower triangular.
+// X = L^{-1} for lower-triangular L (column-major); X is row-major, its upper part zeroed.
 void lower_inverse(const double* L, double* X, int k, hipStream_t s);
 
 }  // namespace krr

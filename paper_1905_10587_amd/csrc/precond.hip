@@ -4,7 +4,7 @@
 // Build, all on the device:
 //   sketch Y (Algorithm 1: K Omega^T through the kernel MVM; Algorithm 2: sparse sketch kernel)
 //   -> pivoted QR of Y^T -> anchors S (first k pivots)
-//   -> K_SS = U^{-1} -> one-sided Jacobi EVD -> drop eigenvalues <= tau * max
+//   -> K_SS = U^{-1} -> EVD (one-sided Jacobi on its Cholesky factor) -> drop eigenvalues <= tau * max
 //   -> C = K(X, X_S) -> W = C V_kept diag(lam_kept)^{-1/2}  (so W W^T = C U C^T)
 //   -> M = W^T W (FP64) -> per beta: Cholesky L L^T = beta I + M (Eq. chol_factor), L^{-1},
 //      G = (beta I + M)^{-1} = L^{-T} L^{-1}.
@@ -44,14 +44,6 @@ __global__ void k_make_T(const double* __restrict__ V, const double* __restrict_
   const int r = (int)(t / kept), c = (int)(t % kept);
   const int j = idx[c];
   T[t] = V[(int64_t)j * k + r] / sqrt(lam[j]);
-}
-
-// out (row-major) = in (column-major) for a k x k matrix: out[r * k + c] = in[c * k + r]
-__global__ void k_colmajor_to_rowmajor(const double* __restrict__ in, int k, double* __restrict__ out) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)k * k) return;
-  const int r = (int)(t / k), c = (int)(t % k);
-  out[t] = in[(int64_t)c * k + r];
 }
 
 __global__ void k_to_f32(const double* __restrict__ a, int64_t n, float* __restrict__ b) {
@@ -323,18 +315,15 @@ static void build_core(krr_precond& P, const double* M, std::vector<DevBuf<doubl
   const int kept = P.kept;
   const int64_t kk = (int64_t)kept * kept;
   for (double beta : P.betas) {
-    DevBuf<double> A(kk, s), L(kk, s), Li(kk, s), Gb(kk, s);
+    DevBuf<double> A(kk, s), L(kk, s), Gb(kk, s);
     hipLaunchKernelGGL(k_add_diag, dim3(nblk(kk)), dim3(256), 0, s, M, kept, beta, A.p);
     KRR_LAUNCH_CHECK();
     const int info = cholesky_lower(A.p, L.p, kept, s);
     if (info != 0)
       throw Error{KRR_ENOTSPD, "Cholesky of beta I + W^T W failed at column " + std::to_string(info - 1) +
                                    " (beta = " + std::to_string(beta) + ")"};
-    lower_inverse(L.p, Li.p, kept, s);
-    // G = L^{-T} L^{-1} = A^T A with A = L^{-1} row-major (lower_inverse writes it column-major)
-    hipLaunchKernelGGL(k_colmajor_to_rowmajor, dim3(nblk(kk)), dim3(256), 0, s, Li.p, kept, A.p);
-    KRR_LAUNCH_CHECK();
-    syrk_tn<double>(A.p, kept, kept, kept, Gb.p, kept, s);
+    lower_inverse(L.p, A.p, kept, s);
+    syrk_tn<double>(A.p, kept, kept, kept, Gb.p, kept, s);   // G = L^{-T} L^{-1}
     G.push_back(std::move(Gb));
     if (Ls) Ls->push_back(std::move(L));
   }
@@ -385,7 +374,7 @@ void build_from_anchors(krr_precond& P, const double* X, hipStream_t s) {
   DevBuf<double> XS((size_t)k * d, s), Kss((size_t)k * k, s), V((size_t)k * k, s), lam(k, s);
   gather_rows(X, n, d, P.S.p, k, XS.p, s);
   kernel_block_colmajor(XS.p, k, XS.p, k, d, P.eps, Kss.p, k, s);
-  P.jacobi_sweeps = jacobi_evd(Kss.p, V.p, lam.p, k, s);
+  P.jacobi_sweeps = jacobi_evd(Kss.p, V.p, lam.p, k, P.prec == KRR_FP64, s);
   std::vector<double> lh(k);
   KRR_CHECK_HIP(hipMemcpyAsync(lh.data(), lam.p, sizeof(double) * k, hipMemcpyDeviceToHost, s));
   KRR_CHECK_HIP(hipStreamSynchronize(s));
