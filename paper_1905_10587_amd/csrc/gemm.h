@@ -28,4 +28,10 @@ template <typename TA>
 void gemm_nn(const TA* A, int64_t lda, const double* B, int64_t ldb, int64_t m, int k, int nb, double* C,
              int64_t ldc, const double* X, int64_t ldx, const double* scale, hipStream_t s);
 
+// The same products in smaller tiles, for sizes of about 1000 in every dimension (FP64):
+//   gemm_tile: C (M x N) = A B (A M x K, B K x N), or X - A B when X is given;  gram_tile: C (N x N) = A^T A (A K x N).
+void gemm_tile(const double* A, int64_t lda, const double* B, int64_t ldb, int M, int K, int N, double* C, int64_t ldc,
+               const double* X, int64_t ldx, hipStream_t s);
+void gram_tile(const double* A, int64_t lda, int K, int N, double* C, int64_t ldc, hipStream_t s);
+
 }  // namespace krr

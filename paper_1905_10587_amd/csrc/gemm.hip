@@ -222,6 +222,93 @@ __global__ __launch_bounds__(256) void k_gemm_nn(const TA* __restrict__ A, int64
       }
 }
 
+// Products whose 128-row tiles would leave the part idle (the pivoted QR's blocks: about 1000 x 1000 over 1000):
+// C (M x N) = A B, or X - A B, in tiles of 32 x 64, two by two waves of 16 x 32.  TRANSA: A is K x M (and with SYM,
+// B == A: tiles entirely below the diagonal are left out, the others stored twice).  About one block per CU, so that
+// nothing but its own loads hides their latency: two stages of 32 contraction rows are in flight in registers while
+// a third is contracted (one stage of 16 ahead: 54 us for 500 x 1024 over 1020).
+template <bool TRANSA, bool SYM, bool EPI>
+__global__ __launch_bounds__(256) void k_gemm_tile(const double* __restrict__ A, int64_t lda, const double* __restrict__ B,
+                                                   int64_t ldb, int M, int K, int N, double* __restrict__ C, int64_t ldc,
+                                                   const double* __restrict__ X, int64_t ldx) {
+  constexpr int BM = 32, BN = 64, TK = 32;
+  __shared__ double As[2][TK][BM + 1];
+  __shared__ double Bs[2][TK][BN + 1];
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  if (SYM && m0 >= n0 + BN) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int wr = wave & 1, wc = wave >> 1;
+  f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+  constexpr int NA = TK * BM / 256, NB = TK * BN / 256;
+  struct Stage {
+    double a[NA], b[NB];
+  };
+  Stage s0, s1;
+  auto load = [&](Stage& s, int k0) {
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+      const int e = tid + 256 * j, r = TRANSA ? e % BM : e / TK, kk = TRANSA ? e / BM : e % TK;
+      s.a[j] = m0 + r < M && k0 + kk < K ? (TRANSA ? A[(int64_t)(k0 + kk) * lda + m0 + r] : A[(int64_t)(m0 + r) * lda + k0 + kk])
+                                         : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int e = tid + 256 * j, kk = e / BN, c = e % BN;
+      s.b[j] = k0 + kk < K && n0 + c < N ? B[(int64_t)(k0 + kk) * ldb + n0 + c] : 0.0;
+    }
+  };
+  auto store = [&](const Stage& s, int buf) {
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+      const int e = tid + 256 * j;
+      if (TRANSA) As[buf][e / BM][e % BM] = s.a[j];
+      else As[buf][e % TK][e / TK] = s.a[j];
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int e = tid + 256 * j;
+      Bs[buf][e / BN][e % BN] = s.b[j];
+    }
+  };
+  auto contract = [&](int buf) {
+#pragma unroll
+    for (int ks = 0; ks < TK; ks += 4) {
+      const double a = As[buf][ks + kq][wr * 16 + r16];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Bs[buf][ks + kq][(wc * 2 + u) * 16 + r16], acc[u], 0, 0, 0);
+    }
+  };
+  const int nsteps = (K + TK - 1) / TK;
+  load(s0, 0);
+  if (nsteps > 1) load(s1, TK);
+  store(s0, 0);
+  __syncthreads();
+  // at stage st (in buffer st % 2) the next one is in a register set, and the one after is loaded into the other
+  for (int st = 0; st < nsteps; st += 2) {
+    if (st + 2 < nsteps) load(s0, (st + 2) * TK);
+    contract(0);
+    if (st + 1 < nsteps) store(s1, 1);
+    __syncthreads();
+    if (st + 1 >= nsteps) break;
+    if (st + 3 < nsteps) load(s1, (st + 3) * TK);
+    contract(1);
+    if (st + 2 < nsteps) store(s0, 0);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = m0 + wr * 16 + 4 * e + kq, j = n0 + (wc * 2 + u) * 16 + r16;
+      if (i >= M || j >= N) continue;
+      const double v = acc[u][e];
+      C[(int64_t)i * ldc + j] = EPI ? X[(int64_t)i * ldx + j] - v : v;
+      if (SYM) C[(int64_t)j * ldc + i] = v;   // (a pair held by two tiles: the same products in the same order)
+    }
+}
+
 int pick_bn(int nb) { return nb <= 16 ? 16 : nb <= 32 ? 32 : nb <= 64 ? 64 : 128; }
 
 // Row split of the A^T B forms: enough blocks to fill the part (about eight per CU), rows per split a
@@ -297,6 +384,24 @@ void gemm_nn(const TA* A, int64_t lda, const double* B, int64_t ldb, int64_t m, 
     case 64: launch_nn<TA, 64>(A, lda, B, ldb, m, k, nb, C, ldc, X, ldx, scale, s); break;
     default: launch_nn<TA, 128>(A, lda, B, ldb, m, k, nb, C, ldc, X, ldx, scale, s); break;
   }
+}
+
+void gemm_tile(const double* A, int64_t lda, const double* B, int64_t ldb, int M, int K, int N, double* C, int64_t ldc,
+               const double* X, int64_t ldx, hipStream_t s) {
+  KRR_REQUIRE(M >= 1 && K >= 1 && N >= 1, "gemm_tile: empty operand");
+  const dim3 g((unsigned)ceil_div(M, 32), (unsigned)ceil_div(N, 64));
+  if (X)
+    hipLaunchKernelGGL((k_gemm_tile<false, false, true>), g, dim3(256), 0, s, A, lda, B, ldb, M, K, N, C, ldc, X, ldx);
+  else
+    hipLaunchKernelGGL((k_gemm_tile<false, false, false>), g, dim3(256), 0, s, A, lda, B, ldb, M, K, N, C, ldc, X, ldx);
+  KRR_LAUNCH_CHECK();
+}
+
+void gram_tile(const double* A, int64_t lda, int K, int N, double* C, int64_t ldc, hipStream_t s) {
+  KRR_REQUIRE(K >= 1 && N >= 1, "gram_tile: empty operand");
+  hipLaunchKernelGGL((k_gemm_tile<true, true, false>), dim3((unsigned)ceil_div(N, 32), (unsigned)ceil_div(N, 64)),
+                     dim3(256), 0, s, A, lda, A, lda, N, K, N, C, ldc, (const double*)nullptr, (int64_t)0);
+  KRR_LAUNCH_CHECK();
 }
 
 template void gemm_tn<double, double>(const double*, int64_t, const double*, int64_t, int64_t, int, int, double*,
