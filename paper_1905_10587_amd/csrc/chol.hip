@@ -1,7 +1,5 @@
 // Blocked Cholesky factorisation and triangular inverse of the preconditioner's cores (Eq. chol_factor), FP64,
 // trailing and off-diagonal products on v_mfma_f64_16x16x4_f64 (operand layouts as in gemm.hip).
-#include <type_traits>
-
 #include "dense.h"
 
 namespace krr {
@@ -23,68 +21,72 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
 // One panel of the right-looking factorisation: columns [j0, j0 + 64) of L.  Block 0 writes the diagonal block's
 // factor, block b > 0 the 64 rows j0 + 64 b .. of L21 = A21 L11^{-T}.  Every block factors the diagonal block
 // itself, its own 64 rows riding along as rows 64 .. 127 of the same elimination, so that a panel is one launch:
-// the 64 elimination steps (one barrier each) bound it, and repeating them in every block costs no time.
+// the serial chain of its 64 steps bounds it, and repeating them in every block costs no time.
 // Wave w holds the columns 16 w .. 16 w + 15 of all 128 rows (lane: rows lane, lane + 64), so that what a step does
-// is the same in a whole wave: nothing, the remaining columns of its own 16, or all 16.  A bad pivot (NaN from there
-// on) is remembered and reported at the end.
-// A is only read, so that the blocks may start in any order; rows and columns past k are those of an identity.
+// is the same in a whole wave; the steps are rolled loops, a wave's own columns shifting down by one register a step.
+// (Broadcasting by lane reads inside a wave instead of LDS and a barrier a step was slower: 36 us.)
+// A bad pivot (NaN from there on) is remembered and reported at the end.  A is only read, so that the blocks may start
+// in any order; rows and columns past k are those of an identity.
 __global__ __launch_bounds__(256) void k_chol_panel(const double* __restrict__ A, double* __restrict__ L, int k, int j0,
                                                     int* __restrict__ info) {
-  __shared__ __align__(16) double col[2][128];
+  __shared__ double col[kCB][128];   // the columns as eliminated, unscaled
+  __shared__ double rsv[kCB];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row0 = j0 + lane, row1 = j0 + 64 * (int)blockIdx.x + lane;   // rows of L11; of L21 (riding along)
   const bool live1 = row1 < k && blockIdx.x != 0;
-  double a[2][16];
+  const int stopped = *info;   // an earlier panel failed: this one computes nothing of use and stores nothing
+  double a0[16], a1[16];
 #pragma unroll
   for (int c = 0; c < 16; ++c) {
-    const int t = j0 + 16 * wave + c;
-    a[0][c] = row0 < k && t <= row0 ? A[(int64_t)t * k + row0] : (row0 == t ? 1.0 : 0.0);
-    a[1][c] = live1 && t < k ? A[(int64_t)t * k + row1] : 0.0;
+    const int t = j0 + 16 * wave + c, tr = t < k ? t : k - 1;
+    const double v0 = A[(int64_t)tr * k + (row0 < k ? row0 : k - 1)], v1 = A[(int64_t)tr * k + (row1 < k ? row1 : k - 1)];
+    a0[c] = row0 < k && t <= row0 ? v0 : (row0 == t ? 1.0 : 0.0);
+    a1[c] = live1 && t < k ? v1 : 0.0;
   }
-  const bool stopped = *info != 0;   // an earlier panel failed: this one computes nothing of use and stores nothing
   int bad = kCB;
-  auto eliminate = [&](auto mine, int j, int c) {   // column j = 16 go + c; mine: of this wave
-    constexpr bool MINE = decltype(mine)::value;
-    const double* cb = col[j & 1];
-    const double ajj = cb[j], rs = rsqrt_nr(ajj);
+  // the columns of earlier waves
+#pragma unroll 1
+  for (int j = 0; j < 16 * wave; ++j) {
+    __syncthreads();
+    const double ajj = col[j][j], rs = rsqrt_nr(ajj);
     if (!(ajj > 0.0) || !isfinite(ajj)) bad = bad < j ? bad : j;
-    const double l0 = cb[lane] * rs, l1 = cb[lane + 64] * rs;
-    const double f0 = l0 * rs, f1 = l1 * rs;
+    const double f0 = col[j][lane] * rs * rs, f1 = col[j][lane + 64] * rs * rs;
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
-      if (MINE && u == c) {
-        a[0][u] = l0;   // final
-        a[1][u] = l1;
-      } else if (!MINE || u > c) {
-        const double at = cb[16 * wave + u];
-        a[0][u] = __builtin_fma(-f0, at, a[0][u]);
-        a[1][u] = __builtin_fma(-f1, at, a[1][u]);
-      }
-    }
-  };
-  for (int go = 0; go < 4; ++go) {
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const int j = 16 * go + c;
-      if (wave == go) {
-        col[c & 1][lane] = a[0][c];
-        col[c & 1][lane + 64] = a[1][c];
-      }
-      __syncthreads();
-      if (wave == go) eliminate(std::true_type{}, j, c);
-      else if (wave > go) eliminate(std::false_type{}, j, c);
+      const double at = col[j][16 * wave + u];
+      a0[u] = __builtin_fma(-f0, at, a0[u]);
+      a1[u] = __builtin_fma(-f1, at, a1[u]);
     }
   }
+  // this wave's own
+#pragma unroll 1
+  for (int c = 0; c < 16; ++c) {
+    const int j = 16 * wave + c;
+    col[j][lane] = a0[0];
+    col[j][lane + 64] = a1[0];
+    __syncthreads();
+    const double ajj = col[j][j], rs = rsqrt_nr(ajj);
+    if (!(ajj > 0.0) || !isfinite(ajj)) bad = bad < j ? bad : j;
+    if (lane == 0) rsv[j] = rs;
+    const double f0 = a0[0] * rs * rs, f1 = a1[0] * rs * rs;
+#pragma unroll
+    for (int u = 1; u < 16; ++u) {
+      const double at = col[j][j + u];   // (past this wave's columns: registers never used)
+      a0[u - 1] = __builtin_fma(-f0, at, a0[u]);
+      a1[u - 1] = __builtin_fma(-f1, at, a1[u]);
+    }
+  }
+  // the later waves' barriers
+#pragma unroll 1
+  for (int j = 16 * wave + 16; j <= kCB; ++j) __syncthreads();
   // the last wave has seen every pivot
   if (wave == 3 && lane == 0 && blockIdx.x == 0 && bad < kCB && !stopped) *info = j0 + bad + 1;
   if (stopped) return;
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int t = j0 + 16 * wave + c;
-    if (blockIdx.x == 0 && row0 < k && t <= row0) L[(int64_t)t * k + row0] = a[0][c];
-    if (live1 && t < k) L[(int64_t)t * k + row1] = a[1][c];
-  }
+  const int r = lane, o = blockIdx.x == 0 ? 0 : 64, row = blockIdx.x == 0 ? row0 : row1;
+#pragma unroll 4
+  for (int c = wave; c < kCB; c += 4)
+    if (j0 + c < k && row < k && (o || r >= c)) L[(int64_t)(j0 + c) * k + row] = col[c][o + r] * rsv[c];
 }
 
 // Trailing update A22 -= L21 L21^T after the panel at j0: one 64 x 64 tile of the lower triangle per block, wave w
@@ -198,6 +200,7 @@ __global__ __launch_bounds__(256) void k_tri_inv_cols(const double* __restrict__
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15, kq = lane >> 4;
   const int cb = c0 / kCB, nb = (k + kCB - 1) / kCB;
   const bool cl = c0 + r16 < k;
+  const int cx = cl ? c0 + r16 : k - 1;   // (dead columns repeat the last one and are not stored)
   for (int e = threadIdx.x; e < cb * kCB * 16; e += 256)
     if (c0 + e % 16 < k) X[(int64_t)(e / 16) * k + c0 + e % 16] = 0.0;
   for (int i = cb; i < nb; ++i) {
@@ -210,7 +213,7 @@ __global__ __launch_bounds__(256) void k_tri_inv_cols(const double* __restrict__
       for (int u = 0; u < 8; ++u) {
         const int t = t0 + 4 * u + kq;
         a[u] = lp[(int64_t)t * k];
-        b[u] = cl ? X[(int64_t)t * k + c0 + r16] : 0.0;
+        b[u] = X[(int64_t)t * k + cx];
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) acc[u & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc[u & 1], 0, 0, 0);

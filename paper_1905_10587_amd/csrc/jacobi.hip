@@ -94,18 +94,25 @@ __device__ __forceinline__ bool idle_pair(int Q, int r, int k) { return Q * kW >
 //
 // What bounds it: the rounds of a sweep are serial, and a round is latency (launch, two passes over 128 KB a
 // workgroup at k = 1000, 8 rotation steps), with NB / 2 workgroups on 256 CUs; hence as many waves per workgroup as
-// the rows feed (NW), all loads of a wave issued together, and those of the second pass before the rotations.
+// the rows feed (NW), all loads of a wave issued together, and those of the second pass before the rotations.  The
+// write-back is the largest part (7.8 of 18.5 us at k = 1000 from one workgroup), so that gridDim.y workgroups share
+// it, each forming the Gram matrix and the rotations for itself; the columns therefore go from A to another buffer
+// O (with 4: 14.8 us; k = 150: 9.0 -> 8.3), past the caches at the largest sizes (14.2).
 template <int NW, bool KEEP>
-__global__ __launch_bounds__(64 * NW) void k_jacobi_pair(double* __restrict__ A, double* __restrict__ Jh, int k, int kp,
-                                                         int NB, int r, unsigned long long* __restrict__ offmax) {
+__global__ __launch_bounds__(64 * NW) void k_jacobi_pair(const double* __restrict__ A, double* __restrict__ O,
+                                                         double* __restrict__ Jh, int k, int kp, int NB, int r,
+                                                         unsigned long long* __restrict__ offmax) {
   __shared__ double red[16][256];
   __shared__ double G[kC2][kC2 + 1], J[kC2][kC2 + 1];
   __shared__ double offw[4];
-  __shared__ int rotated;
   int P, Q;
   block_pair(blockIdx.x, r, NB, P, Q);
-  if (idle_pair(Q, r, k)) return;
   const int tid = threadIdx.x, lane = tid & 63;
+  if (idle_pair(Q, r, k)) {
+    if (blockIdx.y == 0)
+      for (int e = tid; e < kp * kW; e += 64 * NW) O[(int64_t)P * kp * kW + e] = A[(int64_t)P * kp * kW + e];
+    return;
+  }
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kq = lane >> 4;
   const int64_t op = (int64_t)P * kp * kW, oq = (int64_t)Q * kp * kW;
@@ -136,10 +143,11 @@ __global__ __launch_bounds__(64 * NW) void k_jacobi_pair(double* __restrict__ A,
   for (int h = 0; h < GP; ++h)
 #pragma unroll
     for (int e = 0; e < 4; ++e) red[wave + NW * h][(4 * e + kq) * 16 + r16] = acc[h][e];
-  // second pass's operands, issued under the rotations: 16-row tiles w, w + NW, ..; a lane's row r16 of the tile,
-  // columns kq, kq + 4 of either block
+  // second pass's operands, issued under the rotations: of the 16-row tiles y, y + gridDim.y, .. of this workgroup,
+  // wave w takes every NW-th; a lane's row r16 of the tile, columns kq, kq + 4 of either block
   constexpr int TP = 4;
-  const int ntile = kp / 16;
+  const int ntile = kp / 16, sp = gridDim.y;
+  const int t0 = (int)blockIdx.y + sp * wave;
   auto fetch = [&](int t, double (&x)[4]) {
     const int64_t o = (int64_t)(16 * t + r16) * kW + kq;
     x[0] = A[op + o];
@@ -150,7 +158,7 @@ __global__ __launch_bounds__(64 * NW) void k_jacobi_pair(double* __restrict__ A,
   double sa[TP][4];
 #pragma unroll
   for (int u = 0; u < TP; ++u)
-    if (wave + NW * u < ntile) fetch(wave + NW * u, sa[u]);
+    if (t0 + sp * NW * u < ntile) fetch(t0 + sp * NW * u, sa[u]);
   __syncthreads();
   if (tid < 256) {
     double v[4];
@@ -178,10 +186,7 @@ __global__ __launch_bounds__(64 * NW) void k_jacobi_pair(double* __restrict__ A,
   if (wave == 0) {
     double m = offw[0];
     for (int w = 1; w < 4; ++w) m = offw[w] > m ? offw[w] : m;
-    if (lane == 0) {
-      atomicMax(offmax, (unsigned long long)__double_as_longlong(m));
-      rotated = m * m > kTol2;
-    }
+    if (lane == 0 && blockIdx.y == 0) atomicMax(offmax, (unsigned long long)__double_as_longlong(m));
     if (m * m > kTol2) {
       const int a = lane >> 3, b = lane & 7;
       const bool full = r == 0;
@@ -235,8 +240,7 @@ __global__ __launch_bounds__(64 * NW) void k_jacobi_pair(double* __restrict__ A,
     }
   }
   __syncthreads();
-  if (KEEP && tid < 256) Jh[((int64_t)r * (NB / 2) + blockIdx.x) * 256 + tid] = J[tid >> 4][tid & 15];
-  if (!rotated) return;   // nothing to rotate: the columns stay as they are
+  if (KEEP && blockIdx.y == 0 && tid < 256) Jh[((int64_t)r * (NB / 2) + blockIdx.x) * 256 + tid] = J[tid >> 4][tid & 15];
   // second pass: S <- S J
   double jb[4];
 #pragma unroll
@@ -246,12 +250,16 @@ __global__ __launch_bounds__(64 * NW) void k_jacobi_pair(double* __restrict__ A,
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc) d = __builtin_amdgcn_mfma_f64_16x16x4f64(x[kc], jb[kc], d, 0, 0, 0);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) A[mine + (int64_t)(16 * t + 4 * e + kq) * kW] = d[e];
+    for (int e = 0; e < 4; ++e) {
+      double* o = O + mine + (int64_t)(16 * t + 4 * e + kq) * kW;
+      if (NW == 16) __hip_atomic_store(o, d[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else *o = d[e];
+    }
   };
 #pragma unroll
   for (int u = 0; u < TP; ++u)
-    if (wave + NW * u < ntile) apply(wave + NW * u, sa[u]);
-  for (int t = wave + NW * TP; t < ntile; t += NW) {
+    if (t0 + sp * NW * u < ntile) apply(t0 + sp * NW * u, sa[u]);
+  for (int t = t0 + sp * NW * TP; t < ntile; t += sp * NW) {
     double x[4];
     fetch(t, x);
     apply(t, x);
@@ -259,33 +267,31 @@ __global__ __launch_bounds__(64 * NW) void k_jacobi_pair(double* __restrict__ A,
 }
 
 // V <- V J for every pair of the rounds [r0, r1) (J from k_jacobi_pair, round r's at Jh + (r - r0) NB / 2 matrices).
-// The rows of V are independent, so that a workgroup takes `rows` of them through all the rounds in LDS, one barrier
-// a round, instead of a pass over V in every round (k = 1000: 125 rounds in 0.25 ms, against 7 us a round).
-// V: NB kW columns of kp rows, column-major.  LDS: column c at c ld.  Wave w takes pairs w, w + 16, ...; the
-// J of its next pairs is loaded while the current ones are applied.
+// The rows of V are independent, so that a workgroup takes `rows` (1 or 4) of them through all the rounds in LDS, one
+// barrier a round, instead of a pass over V in every round (k = 1000: 7 us a round).  A wave takes pairs w, w + 16,
+// ..: a 4 x 16 by 16 x 16 product as four v_mfma_f64_4x4x4 (operand A: lane l holds row l % 4, column 4 kc + l / 16,
+// the same in its four blocks; B: J[4 kc + l / 16][l % 16]; result: row l / 16, column l % 16), the J of its next pairs
+// loaded while the current ones are applied.  Four rows because every workgroup reads all of J: 252 workgroups at
+// k = 1000 (with 16 rows in 63 workgroups: 3.6 us a round).  V: NB kW columns of kp rows, column-major.
 __global__ __launch_bounds__(1024) void k_apply_rotations(double* __restrict__ V, const double* __restrict__ Jh, int k,
-                                                          int kp, int NB, int r0, int r1, int rows, int ld) {
-  extern __shared__ double vs[];
+                                                          int kp, int NB, int r0, int r1, int rows) {
+  extern __shared__ double vs[];   // column c at rows c
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kq = lane >> 4;
   const int row0 = blockIdx.x * rows, ncol = NB * kW, np = NB / 2;
-  for (int e = tid; e < rows * ncol; e += 1024) {
-    const int c = e / rows, rr = e % rows;
-    vs[c * ld + rr] = row0 + rr < kp ? V[(int64_t)c * kp + row0 + rr] : 0.0;
-  }
-  const int vr = r16 < rows ? r16 : 0;   // rows < 16: the spare lanes repeat row 0 and store nothing
+  for (int e = tid; e < rows * ncol; e += 1024) vs[e] = V[(int64_t)(e / rows) * kp + row0 + e % rows];
+  const int vr = rows == 4 ? lane & 3 : 0;
   auto loadj = [&](int r, int i, double (&j)[4]) {
     const double* p = Jh + ((int64_t)(r - r0) * np + i) * 256 + r16;
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc) j[kc] = p[(4 * kc + kq) * 16];
   };
-  int r = r0, i = wave;
   double jn[4] = {0.0, 0.0, 0.0, 0.0};
-  if (i < np) loadj(r, i, jn);
+  if (wave < np) loadj(r0, wave, jn);
   __syncthreads();
-  for (; r < r1; ++r) {
-    for (i = wave; i < np; i += 16) {
+  for (int r = r0; r < r1; ++r) {
+    for (int i = wave; i < np; i += 16) {
       double j[4];
 #pragma unroll
       for (int kc = 0; kc < 4; ++kc) j[kc] = jn[kc];
@@ -294,24 +300,18 @@ __global__ __launch_bounds__(1024) void k_apply_rotations(double* __restrict__ V
       int P, Q;
       block_pair(i, r, NB, P, Q);
       if (idle_pair(Q, r, k)) continue;
-      f64x4 d = {0.0, 0.0, 0.0, 0.0};
+      double d = 0.0;
 #pragma unroll
       for (int kc = 0; kc < 4; ++kc) {
         const int c = (kc < 2 ? P * kW : Q * kW - kW) + 4 * kc + kq;
-        d = __builtin_amdgcn_mfma_f64_16x16x4f64(j[kc], vs[c * ld + vr], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f64_4x4x4f64(vs[c * rows + vr], j[kc], d, 0, 0, 0);
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {   // result column 4 e + kq of the pair, row r16
-        const int c = (e < 2 ? P * kW : Q * kW - kW) + 4 * e + kq;
-        if (r16 < rows) vs[c * ld + r16] = d[e];
-      }
+      const int c = (r16 < kW ? P * kW : Q * kW - kW) + r16;
+      if (kq < rows) vs[c * rows + kq] = d;
     }
     __syncthreads();
   }
-  for (int e = tid; e < rows * ncol; e += 1024) {
-    const int c = e / rows, rr = e % rows;
-    if (row0 + rr < kp) V[(int64_t)c * kp + row0 + rr] = vs[c * ld + rr];
-  }
+  for (int e = tid; e < rows * ncol; e += 1024) V[(int64_t)(e / rows) * kp + row0 + e % rows] = vs[e];
 }
 
 // Work copy for the factorisation: lower triangle of the symmetric K plus shift on the diagonal
@@ -359,12 +359,14 @@ __global__ __launch_bounds__(256) void k_columns_to_evd(const double* __restrict
 }
 
 template <bool KEEP>
-void jacobi_round(double* A, double* Jh, int k, int kp, int NB, int r, unsigned long long* off, hipStream_t s) {
-  const dim3 g((unsigned)(NB / 2));
+void jacobi_round(const double* A, double* O, double* Jh, int k, int kp, int NB, int r, unsigned long long* off,
+                  hipStream_t s) {
+  // four workgroups a pair while that fits the CUs once
+  const dim3 g((unsigned)(NB / 2), (unsigned)std::max(1, std::min(4, 256 / (NB / 2))));
   // a wave per 64 rows of a pair at most (k = 1000: 36.6 us a round with 4 waves, 16 with 16)
-  if (kp <= 256) hipLaunchKernelGGL((k_jacobi_pair<4, KEEP>), g, dim3(256), 0, s, A, Jh, k, kp, NB, r, off);
-  else if (kp <= 512) hipLaunchKernelGGL((k_jacobi_pair<8, KEEP>), g, dim3(512), 0, s, A, Jh, k, kp, NB, r, off);
-  else hipLaunchKernelGGL((k_jacobi_pair<16, KEEP>), g, dim3(1024), 0, s, A, Jh, k, kp, NB, r, off);
+  if (kp <= 256) hipLaunchKernelGGL((k_jacobi_pair<4, KEEP>), g, dim3(256), 0, s, A, O, Jh, k, kp, NB, r, off);
+  else if (kp <= 512) hipLaunchKernelGGL((k_jacobi_pair<8, KEEP>), g, dim3(512), 0, s, A, O, Jh, k, kp, NB, r, off);
+  else hipLaunchKernelGGL((k_jacobi_pair<16, KEEP>), g, dim3(1024), 0, s, A, O, Jh, k, kp, NB, r, off);
 }
 
 }  // namespace
@@ -376,7 +378,7 @@ int jacobi_evd(const double* K, double* V, double* lam, int k, bool on_factor, h
   NB = std::max(2, NB + (NB & 1));
   const size_t nblocked = (size_t)NB * kp * kW;
   const unsigned gb = (unsigned)ceil_div((int64_t)nblocked, 256);
-  DevBuf<double> A(nblocked, s), R(on_factor ? 0 : nblocked, s);
+  DevBuf<double> A(nblocked, s), A2(nblocked, s), R(on_factor ? 0 : nblocked, s);
   double shift = 0.0;
   if (on_factor) {
     // A numerically singular block (its smallest eigenvalues are rounding noise) is factored with a shift of a few
@@ -396,35 +398,35 @@ int jacobi_evd(const double* K, double* V, double* lam, int k, bool on_factor, h
     hipLaunchKernelGGL(k_identity, dim3(gb), dim3(256), 0, s, k, kp, NB * kW, R.p);
   }
   KRR_LAUNCH_CHECK();
-  DevBuf<unsigned long long> off(1, s);
   // the rotations of `chunk` rounds (64 MB at most) are kept, then applied to rows of R that fit in LDS
   const int64_t jround = (int64_t)(NB / 2) * 256;
   const int chunk = (int)std::min<int64_t>(NB - 1, std::max<int64_t>(1, ((int64_t)8 << 20) / jround));
   DevBuf<double> Jh(on_factor ? 0 : (size_t)(chunk * jround), s);
-  int rows = 16;
-  while (rows > 1 && (size_t)(rows + 1) * NB * kW * sizeof(double) > 150 * 1024) rows /= 2;
-  const int ld = rows > 1 ? rows + 1 : 1;   // an odd stride: the 16 rows and 4 columns of an access fall in all banks
-  const size_t lds = (size_t)ld * NB * kW * sizeof(double);
+  const int rows = (size_t)4 * NB * kW * sizeof(double) <= 150 * 1024 ? 4 : 1;
+  const size_t lds = (size_t)rows * NB * kW * sizeof(double);
   if (!on_factor) {
     KRR_REQUIRE(lds <= 160 * 1024, "k too large for the eigendecomposition");
     KRR_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_apply_rotations),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   }
+  DevBuf<unsigned long long> off(1, s);
   // A sweep's measure is the largest cosine it met before its rotations, and by then convergence is quadratic, with a
   // constant of at most the inverse of the smallest relative gap: 1e-10 leaves less than 1e-13 down to gaps of 1e-7.
   const double stop = on_factor ? 1e-10 : 1e-13;
+  double *cur = A.p, *next = A2.p;
   int sweep = 0;
   for (; sweep < max_sweeps; ++sweep) {
     KRR_CHECK_HIP(hipMemsetAsync(off.p, 0, sizeof(unsigned long long), s));
     for (int r0 = 0; r0 < NB - 1; r0 += on_factor ? NB - 1 : chunk) {
       const int r1 = on_factor ? NB - 1 : std::min(r0 + chunk, NB - 1);
       for (int r = r0; r < r1; ++r) {
-        if (on_factor) jacobi_round<false>(A.p, nullptr, k, kp, NB, r, off.p, s);
-        else jacobi_round<true>(A.p, Jh.p - (int64_t)r0 * jround, k, kp, NB, r, off.p, s);
+        if (on_factor) jacobi_round<false>(cur, next, nullptr, k, kp, NB, r, off.p, s);
+        else jacobi_round<true>(cur, next, Jh.p - (int64_t)r0 * jround, k, kp, NB, r, off.p, s);
+        std::swap(cur, next);
       }
       if (!on_factor)
         hipLaunchKernelGGL(k_apply_rotations, dim3((unsigned)ceil_div(kp, rows)), dim3(1024), lds, s, R.p,
-                           (const double*)Jh.p, k, kp, NB, r0, r1, rows, ld);
+                           (const double*)Jh.p, k, kp, NB, r0, r1, rows);
       KRR_LAUNCH_CHECK();
     }
     unsigned long long h = 0;
@@ -434,7 +436,7 @@ int jacobi_evd(const double* K, double* V, double* lam, int k, bool on_factor, h
     std::memcpy(&offv, &h, sizeof(offv));
     if (offv <= stop) { ++sweep; break; }
   }
-  hipLaunchKernelGGL(k_columns_to_evd, dim3((unsigned)k), dim3(256), 0, s, (const double*)A.p, (const double*)R.p, k, kp,
+  hipLaunchKernelGGL(k_columns_to_evd, dim3((unsigned)k), dim3(256), 0, s, (const double*)cur, (const double*)R.p, k, kp,
                      shift, V, lam);
   KRR_LAUNCH_CHECK();
   return sweep;
