@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "anchors.h"
+#include "scan.h"
 
 namespace krr {
 
@@ -129,58 +130,6 @@ void fps_select(const double* X, int64_t n, int d, int k, int64_t start, int64_t
   }
 }
 
-// ------------------------------------------------------------------ bounding box
-constexpr int64_t kBoxRows = 65536;   // rows per block
-
-// lo/hi[slice * d + c] = min/max of X[i, c] over the rows of one slice.
-__global__ __launch_bounds__(256) void k_bbox(const double* __restrict__ X, int64_t n, int d, double* __restrict__ lo,
-                                              double* __restrict__ hi) {
-  __shared__ double rl[256], rh[256];
-  const int c = blockIdx.y;
-  const int64_t i0 = (int64_t)blockIdx.x * kBoxRows;
-  const int64_t i1 = std::min<int64_t>(i0 + kBoxRows, n);
-  double a = INFINITY, b = -INFINITY;
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
-    const double v = X[i * d + c];
-    a = fmin(a, v);
-    b = fmax(b, v);
-  }
-  rl[threadIdx.x] = a;
-  rh[threadIdx.x] = b;
-  __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h) {
-      rl[threadIdx.x] = fmin(rl[threadIdx.x], rl[threadIdx.x + h]);
-      rh[threadIdx.x] = fmax(rh[threadIdx.x], rh[threadIdx.x + h]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    lo[(int64_t)blockIdx.x * d + c] = rl[0];
-    hi[(int64_t)blockIdx.x * d + c] = rh[0];
-  }
-}
-
-void bounding_box(const double* X, int64_t n, int d, double* lo_host, double* hi_host, hipStream_t s) {
-  const int64_t ns = ceil_div(n, kBoxRows);
-  DevBuf<double> lo(ns * d, s), hi(ns * d, s);
-  hipLaunchKernelGGL(k_bbox, dim3((unsigned)ns, (unsigned)d), dim3(256), 0, s, X, n, d, lo.p, hi.p);
-  KRR_LAUNCH_CHECK();
-  std::vector<double> l(ns * d), h(ns * d);
-  KRR_CHECK_HIP(hipMemcpyAsync(l.data(), lo.p, sizeof(double) * ns * d, hipMemcpyDeviceToHost, s));
-  KRR_CHECK_HIP(hipMemcpyAsync(h.data(), hi.p, sizeof(double) * ns * d, hipMemcpyDeviceToHost, s));
-  KRR_CHECK_HIP(hipStreamSynchronize(s));
-  for (int c = 0; c < d; ++c) {
-    double a = INFINITY, b = -INFINITY;
-    for (int64_t t = 0; t < ns; ++t) {
-      a = std::min(a, l[t * d + c]);
-      b = std::max(b, h[t * d + c]);
-    }
-    lo_host[c] = a;
-    hi_host[c] = b;
-  }
-}
-
 }  // namespace krr
 
 // ================================================================== C ABI
@@ -214,15 +163,15 @@ extern "C" int krr_rank_for_cond(const double* X, int64_t n, int32_t d, double e
     const double arg = Mb * (double)n / (beta * (xi - 1.0));
     KRR_REQUIRE(arg > 1.0, "Mbar n / (beta (xi - 1)) must exceed 1 (delta < 1)");
     hipStream_t s = (hipStream_t)stream;
-    krr::check_finite_device(X, n * (int64_t)d, "X", s);
-    std::vector<double> lo(d), hi(d);
-    krr::bounding_box(X, n, d, lo.data(), hi.data(), s);
+    krr::PointScan ps;
+    const krr::ScanInput in{X, n, d, "X"};
+    krr::scan_inputs(&in, 1, 0, &ps, 0, s);
     // Eq. condbound_gamma with h = sqrt(eps), evaluated in this order: h^{-2} ln(arg), root, 2/pi factor
     const double h = std::sqrt(eps);
     const double g = (2.0 / M_PI) * std::sqrt(std::pow(h, -2.0) * std::log(arg));
     double k = 1.0;
     for (int c = 0; c < d; ++c) {
-      const double q = hi[c] - lo[c];
+      const double q = ps.hi[c] - ps.lo[c];
       if (q_host) q_host[c] = q;
       k *= std::floor(g * q) + 1.0;
     }

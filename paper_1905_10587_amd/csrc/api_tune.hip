@@ -83,13 +83,13 @@ extern "C" int krr_autotune(int32_t d, int32_t R, int32_t prec, int64_t n, int32
     hipLaunchKernelGGL(k_fill_uniform, dim3((unsigned)ceil_div(n * R, 256)), dim3(256), 0, s, V.p, n * R, 99ull);
     KRR_LAUNCH_CHECK();
     const double eps = 0.05 * d;
-    const int dpad = padded_dim(d);
-    DevBuf<double> center(dpad, s);
-    point_mean(X.p, n, d, dpad, center.p, s);
+    PointScan scan;
+    const ScanInput in{X.p, n, d, "X"};
+    scan_inputs(&in, 1, 0, &scan, padded_dim(d), s);
     Staged S;
-    stage_points(S, X.p, n, d, eps, prec, center.p, true, true, s);
+    stage_points(S, X.p, n, d, eps, prec, &scan, true, true, s);
     StagedVec SV;
-    stage_vectors(SV, V.p, n, S.npad, R, prec, s);
+    stage_vectors(SV, V.p, n, S.npad, R, prec, s, kmv_uses_block(prec, d, R, 0));
     DevBuf<double> ws;
     hipEvent_t e0, e1;
     KRR_CHECK_HIP(hipEventCreate(&e0));

@@ -51,27 +51,6 @@ void dev_free(void* p, hipStream_t stream) {
   else (void)hipFreeAsync(p, stream);   // errors on release are not recoverable; ignore
 }
 
-// ------------------------------------------------------------------ non-finite input check
-__global__ void k_count_nonfinite(const double* __restrict__ p, int64_t n, unsigned int* __restrict__ bad) {
-  unsigned int local = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    local |= !isfinite(p[i]);
-  if (local) atomicOr(bad, 1u);
-}
-
-void check_finite_device(const double* p, int64_t count, const char* what, hipStream_t s) {
-  if (count <= 0) return;
-  DevBuf<unsigned int> flag(1, s);
-  KRR_CHECK_HIP(hipMemsetAsync(flag.p, 0, sizeof(unsigned int), s));
-  const int64_t blocks = std::min<int64_t>(ceil_div(count, 256), 4096);
-  hipLaunchKernelGGL(k_count_nonfinite, dim3((unsigned)blocks), dim3(256), 0, s, p, count, flag.p);
-  KRR_LAUNCH_CHECK();
-  unsigned int h = 0;
-  KRR_CHECK_HIP(hipMemcpyAsync(&h, flag.p, sizeof(h), hipMemcpyDeviceToHost, s));
-  KRR_CHECK_HIP(hipStreamSynchronize(s));
-  if (h) throw Error{KRR_EINVAL, std::string(what) + " contains NaN or Inf"};
-}
-
 }  // namespace krr
 
 extern "C" {

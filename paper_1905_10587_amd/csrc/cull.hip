@@ -14,7 +14,6 @@
 #include <map>
 #include <mutex>
 
-#include "anchors.h"
 #include "kmv.h"
 #include "radix_sort.h"
 
@@ -125,23 +124,22 @@ __global__ void k_cull_zero(unsigned long long* c) {
 int cull_mode() { return g_cull_mode.load(); }
 void set_cull_mode(int mode) { g_cull_mode.store(mode < 0 ? -1 : (mode > 2 ? 2 : mode)); }
 
-bool cull_wanted(const double* X, int64_t n, int d, double eps, hipStream_t s) {
+bool cull_wanted(const PointScan& ps, int64_t n, int d, double eps) {
   const int mode = cull_mode();
   if (mode == 0 || mixed_chunks(d) > 4 || n < 2048) return false;   // the symmetric form needs d <= 20
   if (mode >= 1) return true;
   // automatic: only when the data's extent reaches well past the threshold (twice its scaled distance)
-  std::vector<double> lo(d), hi(d);
-  bounding_box(X, n, d, lo.data(), hi.data(), s);
   double diag2 = 0.0;
-  for (int k = 0; k < d; ++k) diag2 += (hi[k] - lo[k]) * (hi[k] - lo[k]);
+  for (int k = 0; k < d; ++k) diag2 += (ps.hi[k] - ps.lo[k]) * (ps.hi[k] - ps.lo[k]);
   return diag2 * kLog2e / eps > 2.0 * kCullQ;
 }
 
-void spatial_order(Staged& st, const double* X, const double* center, hipStream_t s) {
+void spatial_order(Staged& st, const double* X, const PointScan& ps, hipStream_t s) {
   const int64_t n = st.n;
   const int d = st.d, dpad = st.dpad;
-  std::vector<double> lo(d), hi(d), inv(d);
-  bounding_box(X, n, d, lo.data(), hi.data(), s);
+  const double* center = ps.center.p;
+  const std::vector<double>&lo = ps.lo, &hi = ps.hi;
+  std::vector<double> inv(d);
   for (int k = 0; k < d; ++k) inv[k] = hi[k] > lo[k] ? 1.0 / (hi[k] - lo[k]) : 0.0;
   const int b = std::max(1, std::min(20, 63 / d));
   DevBuf<double> lod(d, s), invd(d, s);

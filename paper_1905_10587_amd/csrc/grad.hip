@@ -19,7 +19,8 @@ namespace krr {
 void validate_common(int64_t m, int64_t n, int32_t d, double eps);
 void validate_prec(int32_t prec);
 void kernel_mv_raw(const double* Xt, int64_t m, const double* Xs, int64_t n, int d, double eps, const double* V,
-                   int R, const double* shift, int deriv, int prec, double* U, int64_t ldu, hipStream_t s);
+                   int R, const double* shift, int deriv, int prec, double* U, int64_t ldu, hipStream_t s,
+                   const PointScan* scan);
 
 // out[0] = sum a*b (strided reads a[i*sa], b[i*sb]); single block, fixed order.
 __global__ __launch_bounds__(1024) void k_dot1(const double* __restrict__ a, int sa, const double* __restrict__ b,
@@ -67,30 +68,29 @@ extern "C" int krr_grad(const double* Xtr, int64_t n, const double* ytr, const d
     KRR_REQUIRE(beta > 0 && std::isfinite(beta), "beta must be positive and finite");
     KRR_REQUIRE(tol > 0 && maxit >= 0 && replace_every >= 0, "invalid solver settings");
     hipStream_t s = (hipStream_t)stream;
-    check_finite_device(Xtr, n * (int64_t)d, "Xtr", s);
-    check_finite_device(Xval, m * (int64_t)d, "Xval", s);
-    check_finite_device(ytr, n, "ytr", s);
-    check_finite_device(yval, m, "yval", s);
+    PointScan scan;
+    const ScanInput in[4] = {{Xtr, n, d, "Xtr"}, {Xval, m, d, "Xval"}, {ytr, n, 1, "ytr"}, {yval, m, 1, "yval"}};
+    scan_inputs(in, 4, 0, &scan, padded_dim(d), s);   // (the training points' centre serves every product)
     DevBuf<double> alpha(n, s), lam(n, s), Uv(2 * m, s), rv(m, s), g(n, s), Kpa(n, s), tmp(1, s);
     KRR_CHECK_HIP(hipMemsetAsync(alpha.p, 0, sizeof(double) * n, s));
     KRR_CHECK_HIP(hipMemsetAsync(lam.p, 0, sizeof(double) * n, s));
     // forward solve
     const bool timing = stats != nullptr;
-    PcgResult f = pcg_solve(Xtr, n, d, eps, ytr, 1, &beta, P, tol, maxit, replace_every, prec, alpha.p, timing, s);
+    PcgResult f = pcg_solve(Xtr, n, d, eps, ytr, 1, &beta, P, tol, maxit, replace_every, prec, alpha.p, timing, scan, s);
     if (f.status < 0) return f.status;
     // [K_vt alpha, K'_vt alpha]
-    kernel_mv_raw(Xval, m, Xtr, n, d, eps, alpha.p, 1, nullptr, 2, KRR_FP64, Uv.p, 2, s);
+    kernel_mv_raw(Xval, m, Xtr, n, d, eps, alpha.p, 1, nullptr, 2, KRR_FP64, Uv.p, 2, s, &scan);
     hipLaunchKernelGGL(k_val_residual, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, s, Uv.p, yval, m, rv.p);
     KRR_LAUNCH_CHECK();
     const double L = 0.5 * dot_dev(rv.p, 1, rv.p, 1, m, tmp.p, s);
     const double t1 = dot_dev(rv.p, 1, Uv.p + 1, 2, m, tmp.p, s);    // r_v^T K'_vt alpha
     // g = K_vt^T r_v = K(Xtr, Xval) r_v
-    kernel_mv_raw(Xtr, n, Xval, m, d, eps, rv.p, 1, nullptr, 0, KRR_FP64, g.p, 1, s);
+    kernel_mv_raw(Xtr, n, Xval, m, d, eps, rv.p, 1, nullptr, 0, KRR_FP64, g.p, 1, s, &scan);
     // adjoint solve
-    PcgResult a = pcg_solve(Xtr, n, d, eps, g.p, 1, &beta, P, tol, maxit, replace_every, prec, lam.p, timing, s);
+    PcgResult a = pcg_solve(Xtr, n, d, eps, g.p, 1, &beta, P, tol, maxit, replace_every, prec, lam.p, timing, scan, s);
     if (a.status < 0) return a.status;
     // K' alpha on the training set
-    kernel_mv_raw(Xtr, n, Xtr, n, d, eps, alpha.p, 1, nullptr, 1, KRR_FP64, Kpa.p, 1, s);
+    kernel_mv_raw(Xtr, n, Xtr, n, d, eps, alpha.p, 1, nullptr, 1, KRR_FP64, Kpa.p, 1, s, &scan);
     const double t2 = dot_dev(lam.p, 1, Kpa.p, 1, n, tmp.p, s);      // lambda^T K' alpha
     const double t3 = dot_dev(lam.p, 1, alpha.p, 1, n, tmp.p, s);    // lambda^T alpha
     if (stats) {

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "krr_internal.h"
+#include "scan.h"
 
 #include <string>
 
@@ -46,11 +47,13 @@ int padded_dim(int d);
 // Number of 32-wide K chunks of the split-BF16 cross term for dimension d.
 int mixed_chunks(int d);
 
-// Stage a point set.  center: dpad FP64 on device (translation applied to FP32 and split copies;
-// the kernel is translation invariant).  Pass the same center for targets and sources.
+// Stage a point set.  ps: the scan of the operator's points; its centre is the translation of the staged copies (the
+// kernel is translation invariant; pass the same scan for targets and sources), nullptr: none (FP64 only).
 // sort: stage a square operator's points in spatial order with culling boxes (MIXED only; see Staged).
-void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int prec,
-                  const double* center, bool as_target, bool as_source, hipStream_t s, bool sort = false);
+// parts (FP32): which copies its products will read, the direct kernels' coordinates or the block kernels' split rows.
+enum StageParts { kStageDirect = 1, kStageSplit = 2, kStageAll = 3 };
+void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int prec, const PointScan* ps,
+                  bool as_target, bool as_source, hipStream_t s, bool sort = false, int parts = kStageAll);
 
 // Exact far-tile culling of the symmetric mixed form.  A 16-source step of a wave's 16 NF targets is skipped
 // when every kernel value in it is exactly zero in FP32: the boxes' minimum scaled squared distance exceeds
@@ -60,19 +63,16 @@ void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int
 int cull_mode();
 void set_cull_mode(int mode);
 // Whether a square mixed product of these points should be staged in spatial order under the current mode.
-bool cull_wanted(const double* X, int64_t n, int d, double eps, hipStream_t s);
+bool cull_wanted(const PointScan& ps, int64_t n, int d, double eps);
 // Skip masks for target groups of 16 NF points against 256-source groups (cached in S).
 const uint16_t* cull_masks(const Staged& S, int NF, hipStream_t s);
 // Device counters of skipped 16-source steps (diagonal and off-diagonal super-tiles) of culled launches.
 unsigned long long* cull_counters();
 void cull_reset_counters(hipStream_t s);
-// Mean of the points (FP64), written to center[dpad].
-void point_mean(const double* X, int64_t n, int d, int dpad, double* center, hipStream_t s);
-
 // V (n x R FP64, row-major) -> padded column-block layout used by the kernels.
 struct StagedVec {
   int64_t npad = 0;
-  int R = 0;            // columns padded to a multiple of 8
+  int R = 0;            // columns padded to a multiple of 8 (one column: 1)
   int Rreal = 0;
   // column c of the staged vectors is column cols[c] of the caller's V (row stride ldv), and the products
   // go to the same columns of U; nullptr: columns 0 .. Rreal - 1 of a V with Rreal columns
@@ -95,9 +95,21 @@ void stage_vectors_block(StagedVec& sv, const double* V, int64_t n, int64_t npad
 bool kmv_uses_block(int prec, int d, int R, int deriv);
 // perm: the operator's staged order (Staged::perm), nullptr for the caller's order.  cols (device, R entries)
 // and ldv: stage columns cols[0 .. R) of a V whose rows hold ldv values (a subset of its columns); the kernel
-// MVM then writes its products to those columns of U (one product without the derivative kernel).
-void stage_vectors(StagedVec& sv, const double* V, int64_t n, int64_t npad, int R, int prec,
-                   hipStream_t s, const int64_t* perm = nullptr, const int* cols = nullptr, int ldv = 0);
+// MVM then writes its products to those columns of U (one product without the derivative kernel).  block: the product
+// will take the block path (kmv_uses_block), which stages its own form; only the sizes are set.
+void stage_vectors(StagedVec& sv, const double* V, int64_t n, int64_t npad, int R, int prec, hipStream_t s,
+                   bool block, const int64_t* perm = nullptr, const int* cols = nullptr, int ldv = 0);
+
+// FP64 products of few pairs from the caller's arrays (kmv_small.hip): whether (m, n, d, R, deriv, prec) is one, and
+// the product U (row stride ldu) = K or K' V (+ shift V), deriv as in kmv_launch.  U overlaps no input.  bad: nbad
+// flags of a scan queued before it: where one is set, U is left as it is.
+struct ColumnShift {
+  double v[8];
+  int on;
+};
+bool kmv_small_fits(int64_t m, int64_t n, int d, int R, int deriv, int prec);
+void kmv_small(const double* Xt, int64_t m, const double* Xs, int64_t n, int d, double eps, const double* V, int R,
+               const double* shift, int deriv, double* U, int64_t ldu, const int* bad, int nbad, hipStream_t s);
 
 // Core launcher: U[i, col0 + c] (row stride ldu) for the staged operands.
 //   deriv: 0 K, 1 K', 2 both (K columns first, then K' columns).

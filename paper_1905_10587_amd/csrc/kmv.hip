@@ -17,11 +17,11 @@
 // FP64) that evaluate each pair once for both of its rows.
 // Sources are split across the grid's y dimension; every block writes FP64 partial sums which a
 // finishing kernel adds in a fixed order (deterministic), together with the ridge term.
-#include "anchors.h"
 #include "kmv.h"
 #include "kmv_dispatch.h"
 
 #include <algorithm>
+#include <array>
 #include <cctype>
 #include <map>
 #include <mutex>
@@ -45,35 +45,6 @@ int mixed_chunks(int d) {
 }
 
 // ------------------------------------------------------------------ staging kernels
-__global__ void k_point_sum(const double* __restrict__ X, int64_t n, int d, double* __restrict__ out) {
-  // one block per dimension, fixed-order tree reduction
-  __shared__ double red[256];
-  const int k = blockIdx.x;
-  double s = 0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) s += X[i * d + k];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[k] = red[0] / (double)n;
-}
-
-__global__ void k_zero_tail(double* p, int from, int to) {
-  int i = from + threadIdx.x;
-  if (i < to) p[i] = 0.0;
-}
-
-void point_mean(const double* X, int64_t n, int d, int dpad, double* center, hipStream_t s) {
-  hipLaunchKernelGGL(k_point_sum, dim3(d), dim3(256), 0, s, X, n, d, center);
-  KRR_LAUNCH_CHECK();
-  if (dpad > d) {
-    hipLaunchKernelGGL(k_zero_tail, dim3(1), dim3(128), 0, s, center, d, dpad);
-    KRR_LAUNCH_CHECK();
-  }
-}
-
 // FP64 copy, translated by center when given (the kernel is translation invariant; centred coordinates keep
 // the norms, and so the cancellation of the matrix-core form, small)
 __global__ void k_stage_f64(const double* __restrict__ X, int64_t n, int d, int64_t npad, int dpad,
@@ -116,75 +87,94 @@ __device__ __forceinline__ void split3(double x, uint16_t& h, uint16_t& m, uint1
 //   source side b: [z]h    [z]m    [z]h    [z]l    [z]h    [z]m    | 1 1 1 nh nm nl | 0...
 // with n = -c ||z||^2 split into three parts.  sum_k a_k b_k = -c ||z_t - z_s||^2 up to the
 // dropped m*l, l*m, l*l products (relative size below 2^-24).
+// Eight values (16 bytes) of one point's row per thread, consecutive threads consecutive bytes: a thread per row wrote
+// two bytes at a time, 128 apart (n = 1e5, d = 8: 43 us a side; now 28 for both).  grid.y: sides side0 ..
 __global__ void k_stage_split(const double* __restrict__ X, int64_t n, int d, int64_t npad, int ka,
-                              const double* __restrict__ center, double c, int side,
-                              const int64_t* __restrict__ perm, uint16_t* __restrict__ out) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= npad) return;
-  uint16_t* o = out + i * ka;
-  for (int k = 0; k < ka; ++k) o[k] = 0;
-  if (i >= n) return;
-  const int64_t src = perm ? perm[i] : i;   // staged point i is the caller's point src
-  const uint16_t one = 0x3F80;   // 1.0 in BF16
-  double nz = 0;
-  for (int k = 0; k < d; ++k) {
-    double z = X[src * d + k] - center[k];
-    nz += z * z;
-    double zz = side == 0 ? 2.0 * c * z : z;
-    uint16_t h, m, l;
-    split3(zz, h, m, l);
-    if (side == 0) {
-      o[0 * d + k] = h; o[1 * d + k] = h; o[2 * d + k] = m;
-      o[3 * d + k] = h; o[4 * d + k] = l; o[5 * d + k] = m;
-    } else {
-      o[0 * d + k] = h; o[1 * d + k] = m; o[2 * d + k] = h;
-      o[3 * d + k] = l; o[4 * d + k] = h; o[5 * d + k] = m;
+                              const double* __restrict__ center, double c, int side0,
+                              const int64_t* __restrict__ perm, uint16_t* __restrict__ sa, uint16_t* __restrict__ sb) {
+  const int side = side0 + blockIdx.y, per = ka / 8;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= npad * per) return;
+  const int64_t i = t / per;
+  const int k0 = (int)(t % per) * 8;
+  union {
+    uint16_t h[8];
+    uint4 v;
+  } o;
+  o.v = uint4{0, 0, 0, 0};
+  if (i < n && k0 < 6 * d + 6) {
+    const double* x = X + (perm ? perm[i] : i) * d;   // staged point i is the caller's point perm[i]
+    // part (0 hi, 1 mid, 2 lo) of section s in the layout above
+    const unsigned parts = side == 0 ? 0x120100u : 0x102010u;   // hex digit s (from the right): sections h h m h l m / h m h l h m
+    int sec = k0 / d, dim = k0 - sec * d;
+    double nz = 0;
+    if (k0 + 8 > 6 * d)
+      for (int k = 0; k < d; ++k) {
+        const double z = x[k] - center[k];
+        nz = __builtin_fma(z, z, nz);
+      }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int k = k0 + u;
+      uint16_t h, m, l;
+      if (k < 6 * d) {
+        const double z = x[dim] - center[dim];
+        split3(side == 0 ? 2.0 * c * z : z, h, m, l);
+        const unsigned p = (parts >> (4 * sec)) & 15u;
+        o.h[u] = p == 0 ? h : p == 1 ? m : l;
+        if (++dim == d) { dim = 0; ++sec; }
+      } else if (k < 6 * d + 6) {
+        const int e = k - 6 * d;   // target side: nh nm nl 1 1 1, source side: 1 1 1 nh nm nl
+        split3(-c * nz, h, m, l);
+        const int p = side == 0 ? e : e - 3;
+        o.h[u] = p < 0 || p > 2 ? (uint16_t)0x3F80 : p == 0 ? h : p == 1 ? m : l;
+      }
     }
   }
-  uint16_t h, m, l;
-  split3(-c * nz, h, m, l);
-  const int base = 6 * d;
-  if (side == 0) {
-    o[base + 0] = h; o[base + 1] = m; o[base + 2] = l;
-    o[base + 3] = one; o[base + 4] = one; o[base + 5] = one;
-  } else {
-    o[base + 0] = one; o[base + 1] = one; o[base + 2] = one;
-    o[base + 3] = h; o[base + 4] = m; o[base + 5] = l;
-  }
+  *reinterpret_cast<uint4*>((side == 0 ? sa : sb) + i * ka + k0) = o.v;
 }
 
-void spatial_order(Staged& st, const double* X, const double* center, hipStream_t s);
+void spatial_order(Staged& st, const double* X, const PointScan& ps, hipStream_t s);
 
-void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int prec,
-                  const double* center, bool as_target, bool as_source, hipStream_t s, bool sort) {
+// Rows of a staged set.  Sources are read in tiles of up to 1024.  Targets only: whole blocks of the smallest form that
+// suits them (64 rows mixed, 256 FP64 and FP32), so that 16 predictions do not pay for 1024; kmv_launch takes the
+// largest tile that divides the count.
+static int64_t staged_rows(int64_t n, int prec, bool targets_only) {
+  if (!targets_only || n > 8192) return round_up(n, kRowPad);
+  return round_up(n, prec == KRR_MIXED && n <= 512 ? 64 : 256);
+}
+
+void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int prec, const PointScan* ps,
+                  bool as_target, bool as_source, hipStream_t s, bool sort, int parts) {
   st.n = n;
   st.d = d;
-  st.npad = round_up(n, kRowPad);
+  st.npad = staged_rows(n, prec, as_target && !as_source);
   st.dpad = padded_dim(d);
   st.prec = prec;
   st.eps = eps;
   KRR_REQUIRE(st.dpad > 0, "d exceeds KRR_MAX_D");
   const int64_t tot = st.npad * st.dpad;
   const int blk = 256;
+  const double* center = ps ? ps->center.p : nullptr;
   if (prec == KRR_FP64) {
     st.x64.alloc(tot, s);
     hipLaunchKernelGGL(k_stage_f64, dim3(ceil_div(tot, blk)), dim3(blk), 0, s, X, n, d, st.npad, st.dpad, center,
                        st.x64.p);
     KRR_LAUNCH_CHECK();
-    // the box of the points bounds every squared distance by diag2 and the staged squared norms by max2
-    std::vector<double> lo(d), hi(d), ctr(d, 0.0);
-    if (center) KRR_CHECK_HIP(hipMemcpyAsync(ctr.data(), center, sizeof(double) * d, hipMemcpyDeviceToHost, s));
-    bounding_box(X, n, d, lo.data(), hi.data(), s);   // synchronises the stream
-    double diag2 = 0.0, max2 = 0.0;
-    for (int k = 0; k < d; ++k) {
-      diag2 += (hi[k] - lo[k]) * (hi[k] - lo[k]);
-      const double a = lo[k] - ctr[k], b = hi[k] - ctr[k];
-      max2 += std::max(a * a, b * b);
+    if (ps && as_target && as_source) {
+      // the box of the points bounds every squared distance by diag2 and the staged squared norms by max2
+      double diag2 = 0.0, max2 = 0.0;
+      for (int k = 0; k < d; ++k) {
+        diag2 += (ps->hi[k] - ps->lo[k]) * (ps->hi[k] - ps->lo[k]);
+        const double a = ps->lo[k] - ps->mean[k], b = ps->hi[k] - ps->mean[k];
+        max2 += std::max(a * a, b * b);
+      }
+      const double c = kLog2e / eps;
+      st.q_floor = c * diag2 <= 1000.0 && c * max2 <= 1e10;
     }
-    const double c = kLog2e / eps;
-    st.q_floor = c * diag2 <= 1000.0 && c * max2 <= 1e10;
   } else {
-    if (prec == KRR_FP32) {
+    KRR_REQUIRE(center, "internal: FP32 and mixed operators are staged about a centre");
+    if (prec == KRR_FP32 && (parts & kStageDirect)) {
       st.x32.alloc(tot, s);
       const double scale = std::sqrt(kLog2e / eps);
       hipLaunchKernelGGL(k_stage_f32, dim3(ceil_div(tot, blk)), dim3(blk), 0, s, X, n, d, st.npad, st.dpad,
@@ -196,18 +186,14 @@ void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int
     const double c = kLog2e / eps;
     if (sort) {
       KRR_REQUIRE(prec == KRR_MIXED && as_target && as_source, "spatial order is for square mixed operators");
-      spatial_order(st, X, center, s);
+      spatial_order(st, X, *ps, s);
     }
-    if (as_target) {
-      st.sa.alloc(st.npad * st.ka, s);
-      hipLaunchKernelGGL(k_stage_split, dim3(ceil_div(st.npad, blk)), dim3(blk), 0, s, X, n, d, st.npad,
-                         st.ka, center, c, 0, (const int64_t*)st.perm.p, st.sa.p);
-      KRR_LAUNCH_CHECK();
-    }
-    if (as_source) {
-      st.sb.alloc((st.npad + kPrefetchRows) * st.ka, s);   // padding rows: read by the last prefetch only
-      hipLaunchKernelGGL(k_stage_split, dim3(ceil_div(st.npad, blk)), dim3(blk), 0, s, X, n, d, st.npad,
-                         st.ka, center, c, 1, (const int64_t*)st.perm.p, st.sb.p);
+    if (prec == KRR_MIXED || (parts & kStageSplit)) {
+      if (as_target) st.sa.alloc(st.npad * st.ka, s);
+      if (as_source) st.sb.alloc((st.npad + kPrefetchRows) * st.ka, s);   // padding rows: read by the last prefetch only
+      hipLaunchKernelGGL(k_stage_split, dim3((unsigned)ceil_div(st.npad * (st.ka / 8), blk), as_target && as_source ? 2u : 1u),
+                         dim3(blk), 0, s, X, n, d, st.npad, st.ka, center, c, as_target ? 0 : 1,
+                         (const int64_t*)st.perm.p, st.sa.p, st.sb.p);
       KRR_LAUNCH_CHECK();
     }
   }
@@ -225,15 +211,16 @@ __global__ void k_stage_vec(const double* __restrict__ V, int64_t n, int R, int6
   if (o32) o32[idx] = (float)v;
 }
 
-void stage_vectors(StagedVec& sv, const double* V, int64_t n, int64_t npad, int R, int prec,
-                   hipStream_t s, const int64_t* perm, const int* cols, int ldv) {
+void stage_vectors(StagedVec& sv, const double* V, int64_t n, int64_t npad, int R, int prec, hipStream_t s,
+                   bool block, const int64_t* perm, const int* cols, int ldv) {
   KRR_REQUIRE(!cols || (ldv >= R && !perm), "internal: a column subset needs its row stride and the caller's order");
   sv.npad = npad;
   sv.Rreal = R;
   sv.cols = cols;
   sv.ldv = cols ? ldv : R;
-  // column chunks are at most 8 wide; FP64 with more than 8 columns pads to 16 for the matrix-core kernel
-  sv.R = (int)round_up(R, prec == KRR_FP64 && R > 8 ? 16 : 8);
+  // one column is packed; several: column chunks are at most 8 wide; FP64 with more than 8 columns pads to 16 for the
+  // matrix-core kernel
+  sv.R = R == 1 ? 1 : (int)round_up(R, prec == KRR_FP64 && R > 8 ? 16 : 8);
   const int64_t tot = npad * sv.R;
   const size_t cap = (size_t)(npad + kPrefetchRows) * sv.R;   // padding rows: read by the last prefetch only
   // grow only: a solve whose active columns shrink reuses the buffer, so products captured into a graph after
@@ -243,6 +230,7 @@ void stage_vectors(StagedVec& sv, const double* V, int64_t n, int64_t npad, int 
   } else {
     if (sv.v32.n < cap) sv.v32.alloc(cap, s);
   }
+  if (block) return;   // the matrix-core block path lays out its own; fewer active columns may yet leave it
   hipLaunchKernelGGL(k_stage_vec, dim3(ceil_div(tot, 256)), dim3(256), 0, s, V, n, R, npad, sv.R, perm, cols,
                      sv.ldv, sv.v64.p, sv.v32.p);
   KRR_LAUNCH_CHECK();
@@ -318,12 +306,14 @@ void stage_vectors_block(StagedVec& sv, const double* V, int64_t n, int64_t npad
 // ------------------------------------------------------------------ finishing kernel
 // U[i, oc] = sum_s part[s, i, pc] (+ shift[oc] * Vraw[i, oc] on K columns), where the part row holds
 // the K columns at [0, Rp) and the K' columns at [Rp, 2 Rp).
-struct ShiftArg {
-  double v[256];
+template <int N>
+struct ShiftArg {   // (a kernel argument: 8 values where they do, the 2 KB of 256 cost microseconds a launch)
+  double v[N];
 };
 
+template <int N>
 __global__ void k_kmv_finish(const double* __restrict__ part, int S, int64_t mpad, int Rp, int Rout,
-                             int deriv, int64_t m, int R, int has_shift, ShiftArg sh,
+                             int deriv, int64_t m, int R, int has_shift, ShiftArg<N> sh,
                              const double* __restrict__ Vraw, const int64_t* __restrict__ perm,
                              const int* __restrict__ cols, int ldv, double* __restrict__ U, int64_t ldu) {
   const int Rcols = deriv == 2 ? 2 * R : R;
@@ -410,6 +400,7 @@ static bool shared_block_fits(int R) {
 
 KmvChoice kmv_lookup(int prec, int d, int R, int64_t n, bool square) {
   std::lock_guard<std::mutex> lk(g_mu);
+  if (g_table.empty()) return KmvChoice{};
   if (n > 0) {
     auto it = g_table.find(exact_key(d, R, prec, n, square));
     if (it != g_table.end()) {
@@ -588,12 +579,13 @@ static int64_t device_cus() {
 }
 
 // Resident blocks of a kernel configuration on the current device (blocks per CU x CUs), cached by key.
+using LaunchKey = std::array<int, 6>;   // device, precision, d, shape class, variant and tile rows, derivative form
 template <typename Query>
-static int64_t resident_blocks(Query query, const std::string& key) {
+static int64_t resident_blocks(Query query, LaunchKey k) {
   int dev = 0;
   KRR_CHECK_HIP(hipGetDevice(&dev));
-  const std::string k = std::to_string(dev) + "/" + key;
-  static std::map<std::string, int64_t> cache;
+  k[0] = dev;
+  static std::map<LaunchKey, int64_t> cache;
   {
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = cache.find(k);
@@ -626,9 +618,9 @@ bool kernel_times_matrix_f64(const double* Xt, int64_t m, const double* Xs, int6
   stage_points(St, Xt, m, d, eps, KRR_FP64, nullptr, true, false, s);
   stage_points(Ss, Xs, k, d, eps, KRR_FP64, nullptr, false, true, s);
   const int Rp = (int)round_up(ncol, 16);
-  DevBuf<double> V((size_t)Ss.npad * Rp, s);
-  hipLaunchKernelGGL(k_pad_matrix, dim3((unsigned)ceil_div(Ss.npad * Rp, 256)), dim3(256), 0, s, T, k, ldt, ncol,
-                     Ss.npad, Rp, V.p);
+  const int64_t kp = round_up(k, 16);   // the kernel's source tile: not the whole padding (k = 150: 160 of 1024)
+  DevBuf<double> V((size_t)kp * Rp, s);
+  hipLaunchKernelGGL(k_pad_matrix, dim3((unsigned)ceil_div(kp * Rp, 256)), dim3(256), 0, s, T, k, ldt, ncol, kp, Rp, V.p);
   KRR_LAUNCH_CHECK();
   // block width 16 NRG: per 4-source step NRG MFMAs (64 cycles each) plus the pair's distance and exp
   // (about 112 VALU cycles), over ceil(Rp / 16 NRG) column blocks
@@ -638,7 +630,7 @@ bool kernel_times_matrix_f64(const double* Xt, int64_t m, const double* Xs, int6
     const double cost = (double)ceil_div(Rp, 16 * nr) * (64.0 * nr + 112.0);
     if (cost < best * (1 - 1e-9)) { best = cost; NRG = nr; }
   }
-  KmvGrid g{dim3((unsigned)(St.npad / 64), 1u, (unsigned)ceil_div(Rp, 16 * NRG)), Ss.npad, Ss.npad, St.npad, Rp,
+  KmvGrid g{dim3((unsigned)(St.npad / 64), 1u, (unsigned)ceil_div(Rp, 16 * NRG)), kp, kp, St.npad, Rp,
             (int)ldw};
   g.m_store = m;
   g.n_store = ncol;
@@ -694,6 +686,8 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
     NRC = std::min(kBlockNRC[vb], nrc_max);
     stage_vectors_block(V, Vraw, S.n, S.npad, R, shared ? 32 : 16 * NRC, prec == KRR_MIXED ? 2 : 3, s);
     Rpart = V.Rb;
+    while (T.npad % (64 * NT)) NT /= 2;
+    if (T.npad % (64 * shared_fw)) shared_fw = 1;
     rows = shared ? 64 * shared_fw : 64 * NT;
     gz = shared ? (int)ceil_div(V.Rb, 128) : V.Rb / (16 * NRC);   // shared form: 128 columns per block
   } else if (prec == KRR_MIXED) {
@@ -709,6 +703,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
     } else {
       form = var >= 7 ? 2 : var >= 4 ? 1 : 0;
       NF = std::min(var >= 7 ? kNF[var - 6] : var >= 4 ? kNF[var - 3] : kNF[var], mixed_max_nf(nch));
+      while (T.npad % (64 * NF)) NF /= 2;   // few targets are staged in whole blocks of a smaller tile (same results)
       if (!mixed_has_pp(nch) || NF < 2) form = 0;   // no pipelined form: the plain kernel, same NF
     }
     rows = 64 * NF;
@@ -738,6 +733,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
       RC = R >= 32 && Rp % 32 == 0 ? 32 : 16;
       TM = 1;
     }
+    while (!sym && T.npad % (256 * TM)) TM /= 2;   // few targets are staged in whole blocks of a smaller tile
     rows = f64sm ? 64 * NF : 256 * TM;
     gz = (int)ceil_div(R, RC);   // real columns only (Rp is padded to 8)
     KRR_REQUIRE(Rp % RC == 0, "internal: column chunk does not divide the padded column count");
@@ -784,7 +780,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
         q.occ = occ;
         KRR_REQUIRE(run(q), "kernel variant not instantiated for this shape");
       },
-      vkey(T.d, R, prec) + ":" + std::to_string(variant) + ":" + std::to_string(DV));
+      LaunchKey{0, prec, T.d, rclass(prec, R), variant * 4096 + (int)rows, DV});
   int64_t smax = std::max<int64_t>(1, nsrc / 256);
   if (block) smax = std::min<int64_t>(smax, std::max<int64_t>(1, ((int64_t)1 << 28) / (T.npad * (int64_t)RoutK)));
   const int64_t per_split = gx * gz;
@@ -820,12 +816,15 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
     const int64_t cus = device_cus();
     int64_t bestE = 0;
     double bestc = 1e300;
-    for (int64_t E : {1024, 2048, 3072, 4096, 6144, 8192, 12288, 16384}) {
-      if (E % rows) continue;
+    for (int64_t E : {256, 512, 1024, 2048, 3072, 4096, 6144, 8192, 12288, 16384}) {
+      // (mixed: the super-tile decides which pairs are summed as rows only, in FP32, so it stays as it was; FP64 takes
+      // the small ones where 1024 leaves CUs idle, with a block's start counted as about 30000 pairs)
+      if (E % rows || (prec != KRR_FP64 && E < 1024)) continue;
       const int64_t ns = ceil_div(T.npad, E);
       if ((double)ns * T.npad * 8.0 > 2.2e9 && E != 16384) continue;
       const int64_t items = ns * (ns + 1) / 2;
-      const double cost = (double)std::max<int64_t>(ceil_div(items, cus), 2) * (double)E * (double)E;
+      const double cost = (double)std::max<int64_t>(ceil_div(items, cus), 2) *
+                          ((double)E * (double)E + (prec == KRR_FP64 ? 30000.0 : 0.0));
       if (cost < bestc * (1 - 1e-9)) { bestc = cost; bestE = E; }
     }
     // a requested edge: one of the candidates, a multiple of the target tile, partials near 2 GB at most
@@ -849,15 +848,18 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
   if (kev) KRR_CHECK_HIP(hipEventRecord(kev[1], s));
   KRR_REQUIRE(ok, "kernel variant not instantiated for this shape");
   KRR_LAUNCH_CHECK();
-  ShiftArg sh{};
   const int has_shift = shift_host != nullptr;
-  if (has_shift)
-    for (int c = 0; c < R; ++c) sh.v[c] = shift_host[c];
   const int Rcols = deriv == 2 ? 2 * R : R;
   const int64_t tot = T.n * Rcols;
-  hipLaunchKernelGGL(k_kmv_finish, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, part.p, (int)split,
-                     T.npad, RpK, RoutK, deriv, T.n, R, has_shift, sh, Vraw, (const int64_t*)T.perm.p, V.cols,
-                     V.cols ? V.ldv : R, U, ldu);
+  auto finish = [&](auto sh) {
+    if (has_shift)
+      for (int c = 0; c < R; ++c) sh.v[c] = shift_host[c];
+    hipLaunchKernelGGL((k_kmv_finish<sizeof(sh) / sizeof(double)>), dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s,
+                       part.p, (int)split, T.npad, RpK, RoutK, deriv, T.n, R, has_shift, sh, Vraw,
+                       (const int64_t*)T.perm.p, V.cols, V.cols ? V.ldv : R, U, ldu);
+  };
+  if (R <= 8) finish(ShiftArg<8>{});
+  else finish(ShiftArg<256>{});
   KRR_LAUNCH_CHECK();
 }
 

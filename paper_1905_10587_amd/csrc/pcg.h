@@ -4,6 +4,7 @@
 #include <vector>
 
 #include "krr_internal.h"
+#include "scan.h"
 
 namespace krr {
 
@@ -16,6 +17,6 @@ struct PcgResult {
 
 PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double* Y, int R, const double* betas,
                     const krr_precond* P, double tol, int maxit, int replace_every, int prec, double* x,
-                    bool timing, hipStream_t s);
+                    bool timing, const PointScan& scan, hipStream_t s);   // scan: of X
 
 }  // namespace krr

@@ -475,21 +475,23 @@ struct Operator {
   const double* X = nullptr;
   int64_t n = 0;
   int R = 0;
-  void init(const double* X_, int64_t n_, int d, double eps, int prec_, const double* center, int R_, hipStream_t s) {
+  void init(const double* X_, int64_t n_, int d, double eps, int prec_, const PointScan& scan, int R_, hipStream_t s) {
     X = X_;
     n = n_;
     prec = prec_;
     R = R_;
     // one-column mixed operators may be staged in spatial order for exact far-tile culling
-    const bool sort = prec == KRR_MIXED && R == 1 && cull_wanted(X, n, d, eps, s);
-    stage_points(S, X, n, d, eps, prec, center, true, true, s, sort);
+    const bool sort = prec == KRR_MIXED && R == 1 && cull_wanted(scan, n, d, eps);
+    // (several columns: a block solve's active columns may shrink out of the block path)
+    stage_points(S, X, n, d, eps, prec, &scan, true, true, s, sort, R == 1 ? kStageDirect : kStageAll);
   }
   // out = (K + diag(shift)) v   (shift may be null).  cols (device, ncols entries): only those columns of v are
   // multiplied, into the same columns of out (shift then holds their ncols shifts); the others are not written.
   void apply(const double* v, const double* shift, double* out, hipStream_t s, const hipEvent_t* kev = nullptr,
              const int* cols = nullptr, int ncols = 0) {
-    if (cols) stage_vectors(V, v, n, S.npad, ncols, prec, s, nullptr, cols, R);
-    else stage_vectors(V, v, n, S.npad, R, prec, s, S.perm.p);
+    const bool block = kmv_uses_block(prec, S.d, cols ? ncols : R, 0);
+    if (cols) stage_vectors(V, v, n, S.npad, ncols, prec, s, block, nullptr, cols, R);
+    else stage_vectors(V, v, n, S.npad, R, prec, s, block, S.perm.p);
     kmv_launch(S, S, V, 0, shift, v, prec, out, R, s, -1, &ws, kev);
   }
 };
@@ -516,7 +518,7 @@ static bool use_graph_cycles(int64_t n, int R, int replace_every, bool timing) {
 
 PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double* Y, int R, const double* betas,
                     const krr_precond* P, double tol, int maxit, int replace_every, int prec, double* x,
-                    bool timing, hipStream_t s) {
+                    bool timing, const PointScan& scan, hipStream_t s) {
   using clk = std::chrono::steady_clock;
   const auto t_start = clk::now();
   PcgResult res;
@@ -532,14 +534,11 @@ PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double*
     KRR_REQUIRE(prec == KRR_FP64 || P->W32.p, "FP32/mixed solve needs a preconditioner built with FP32 factors");
   }
   const int64_t nR = n * R;
-  const int dpad = padded_dim(d);
-  DevBuf<double> center(dpad, s);
-  point_mean(X, n, d, dpad, center.p, s);
   Operator Aw, A64;
-  Aw.init(X, n, d, eps, prec, center.p, R, s);
+  Aw.init(X, n, d, eps, prec, scan, R, s);
   Operator* Atrue = &Aw;
   if (prec != KRR_FP64) {
-    A64.init(X, n, d, eps, KRR_FP64, center.p, R, s);
+    A64.init(X, n, d, eps, KRR_FP64, scan, R, s);
     Atrue = &A64;
   }
   WoodburyWork ww;
@@ -1148,11 +1147,11 @@ extern "C" int krr_pcg_solve(const double* X, int64_t n, int32_t d, double eps, 
     KRR_REQUIRE(replace_every >= 0, "replace_every must be >= 0");
     for (int c = 0; c < R; ++c) KRR_REQUIRE(betas[c] > 0 && std::isfinite(betas[c]), "beta must be positive and finite");
     hipStream_t s = (hipStream_t)stream;
-    krr::check_finite_device(X, n * (int64_t)d, "X", s);
-    krr::check_finite_device(Yrhs, n * (int64_t)R, "y", s);
-    krr::check_finite_device(alpha, n * (int64_t)R, "initial alpha", s);
+    krr::PointScan scan;
+    const krr::ScanInput in[3] = {{X, n, d, "X"}, {Yrhs, n, R, "y"}, {alpha, n, R, "initial alpha"}};
+    krr::scan_inputs(in, 3, 0, &scan, krr::padded_dim(d), s);
     krr::PcgResult res =
-        krr::pcg_solve(X, n, d, eps, Yrhs, R, betas, P, tol, maxit, replace_every, prec, alpha, timing != 0, s);
+        krr::pcg_solve(X, n, d, eps, Yrhs, R, betas, P, tol, maxit, replace_every, prec, alpha, timing != 0, scan, s);
     for (int c = 0; c < R; ++c) {
       iters[c] = res.iters[c];
       relres[c] = res.relres[c];

@@ -33,7 +33,8 @@ namespace krr {
 void validate_common(int64_t m, int64_t n, int32_t d, double eps);
 void validate_prec(int32_t prec);
 void kernel_mv_raw(const double* Xt, int64_t m, const double* Xs, int64_t n, int d, double eps, const double* V,
-                   int R, const double* shift, int deriv, int prec, double* U, int64_t ldu, hipStream_t s);
+                   int R, const double* shift, int deriv, int prec, double* U, int64_t ldu, hipStream_t s,
+                   const PointScan* scan);
 
 // ------------------------------------------------------------------ small kernels
 // T (k x kept, row-major) = V_kept diag(lam_kept)^{-1/2}; V column-major (eigenvector j at V + j k)
@@ -284,6 +285,9 @@ void sketch_dense(const double* X, int64_t n, int d, double eps, const double* o
                   hipStream_t s) {
   constexpr int kChunk = 256;
   DevBuf<double> Oc(l > kChunk ? (size_t)n * kChunk : 0, s);
+  PointScan scan;
+  const ScanInput in{X, n, d, "X"};
+  scan_inputs(&in, 1, 0, &scan, padded_dim(d), s);
   for (int c0 = 0; c0 < l; c0 += kChunk) {
     const int rc = std::min(kChunk, l - c0);
     const double* V = omega;
@@ -292,7 +296,7 @@ void sketch_dense(const double* X, int64_t n, int d, double eps, const double* o
                                      (size_t)n, hipMemcpyDeviceToDevice, s));
       V = Oc.p;
     }
-    kernel_mv_raw(X, n, X, n, d, eps, V, rc, nullptr, 0, prec, Y + c0, l, s);
+    kernel_mv_raw(X, n, X, n, d, eps, V, rc, nullptr, 0, prec, Y + c0, l, s, &scan);
   }
 }
 
