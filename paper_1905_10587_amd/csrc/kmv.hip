@@ -833,11 +833,24 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
       bestE = split_req;
     const int64_t ns = ceil_div(T.npad, bestE);
     const int64_t items = ns * (ns + 1) / 2;
-    split = ns;
+    // Mixed: a super-tile may be shared by sub^2 blocks without another result.  The same cost, with a block's start
+    // and the pass over the partials (about 0.055 pairs a byte / 8) counted: below some 40000 points blocks are wanting.
+    int sub = 1;
+    if (prec == KRR_MIXED) {
+      auto cost = [&](int64_t b) {
+        const int64_t e = bestE / b;
+        return (double)std::max<int64_t>(ceil_div(items * b * b, cus), 2) * ((double)e * (double)e + 30000.0) +
+               0.055 * (double)ceil_div(T.npad, e) * (double)T.npad;
+      };
+      for (int b = 2; bestE % (512 * b) == 0 && (bestE / b) % rows == 0; b *= 2)
+        if (cost(b) < cost(sub)) sub = b;
+    }
+    split = ceil_div(T.npad, bestE / sub);
     src_len = bestE;
-    g = KmvGrid{dim3((unsigned)(8 * ceil_div(items, 8))), src_len, nsrc, T.npad, RpK, RoutK};
+    g = KmvGrid{dim3((unsigned)(8 * ceil_div(items * sub * sub, 8))), src_len, nsrc, T.npad, RpK, RoutK};
     g.E = (int)bestE;
     g.NS = (int)ns;
+    g.sub = sub;
   }
   const size_t need = (size_t)split * T.npad * RoutK;
   if (part.n < need) part.alloc(need, s);

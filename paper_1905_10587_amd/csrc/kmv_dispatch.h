@@ -12,7 +12,7 @@ struct KmvGrid {
   // When set, the launcher writes the kernel's resident blocks per CU here instead of launching.
   int* occ = nullptr;
   // symmetric form: super-tile edge and super-tiles per side (grid.x = 8 * ceil(NS (NS + 1) / 16))
-  int E = 0, NS = 0;
+  int E = 0, NS = 0, sub = 1;
   // FP64 matrix-core form writing a final result in place: rows >= m_store and columns >= n_store are not
   // stored (0: all padded rows, Rp columns)
   int64_t m_store = 0;

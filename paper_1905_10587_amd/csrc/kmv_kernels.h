@@ -1039,17 +1039,35 @@ __global__ __launch_bounds__(256) void k_kmv_mixed_lds(const uint4* __restrict__
   }
 }
 
+// Lane 16 k + i: the sum of c[k] over the four lanes 16 l + i, as (l = 0 + l = 1) + (l = 2 + l = 3).  Two rows change
+// places per swap, so four values take three swaps and three additions.
+__device__ __forceinline__ float four_steps(const float* c) {
+  auto sum = [](auto s) {
+    const unsigned lo = s[0], hi = s[1];
+    return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+  };
+  auto bits = [](float x) { return __builtin_bit_cast(unsigned, x); };
+  const float ab = sum(__builtin_amdgcn_permlane16_swap(bits(c[0]), bits(c[1]), false, false));
+  const float cd = sum(__builtin_amdgcn_permlane16_swap(bits(c[2]), bits(c[3]), false, false));
+  return sum(__builtin_amdgcn_permlane32_swap(bits(ab), bits(cd), false, false));
+}
+
 // Symmetric form for the square product u = K(X, X) v (one column), using K_ij = K_ji.  The index range is
 // cut into super-tiles of E points; block b owns one pair (r, c), r <= c, of the upper triangle and
 // evaluates the E x E tile once:
 //   row sums  sum_{j in c} K_ij v_j  for i in r  -> part[c][i],
 //   col sums  sum_{i in r} K_ij v_i  for j in c  -> part[r][j]   (off-diagonal pairs only).
+// With sub > 1 a pair of super-tiles is shared by sub^2 blocks, one for each pair of its parts of e = E / sub points (a
+// multiple of 512, so that each FP32 sum keeps its terms); r, c and the slots then count parts, and a diagonal
+// super-tile's parts are all summed by rows.  At 20000 points, d = 16, the 210 super-tiles of 1024 leave one wave to a
+// SIMD: 130 us; in parts of 512, 100 us, where
+// issue binds (a CU's two blocks take 200 cycles per 256 pairs and SIMD, 64 of them MFMA, which VALU work hardly overlaps).
 // Every slot part[s][i] (s < NS) receives exactly one contribution, so the FP64 finishing pass sums NS
 // partials per row in a fixed order.  Inside a block the pipelined LDS-staged tile loop of
-// k_kmv_mixed_lds runs once per target tile of 64 NF points; each lane's column partial for one step (its
-// source, over its 4 NF targets: FP32 over NF x 4 products) goes to LDS, and at the end of each source
-// tile the 16 partials of a source (4 waves x 4 lane groups) are added pairwise in FP32 and the sum is
-// added to the source's FP64 slot.  Row sums are folded from FP32 into FP64 every 512 sources.
+// k_kmv_mixed_lds runs once per target tile of 64 NF points; a lane's column partials (its source of one step, over its
+// 4 NF targets: FP32 over NF x 4 products) are added pairwise in FP32, first the four lane groups' (row exchanges, four
+// steps together), then through LDS the four waves' at the end of the source tile, and the sum is added to the source's
+// FP64 slot.  Row sums are folded from FP32 into FP64 every 512 sources.
 // Items are laid out so that each XCD (blocks b = x mod 8) walks a contiguous run of the triangle in
 // column order.
 //
@@ -1059,9 +1077,9 @@ __global__ __launch_bounds__(256) void k_kmv_mixed_lds(const uint4* __restrict__
 // Adding exact zeros changes no sum, so the result is bit for bit that of the unculled kernel.  The skipped
 // steps are counted (ccount[0]: diagonal super-tiles, ccount[1]: the others).
 template <int NCH, int NF, bool CULL>
-// (two resident blocks per CU: the register budget is held to 256 per lane; NF 8 spills a few values)
+// (two resident blocks per CU: the register budget is held to 256 per lane with four waves)
 __global__ __launch_bounds__(256, 2) void k_kmv_mixed_sym(const uint4* __restrict__ A, const uint4* __restrict__ B,
-                                                       const float* __restrict__ v, int Rp, int E, int NS,
+                                                       const float* __restrict__ v, int Rp, int e_len, int sub, int NS,
                                                        int64_t npad, double* __restrict__ part, int Rout,
                                                        const uint16_t* __restrict__ cmask, int64_t ngs,
                                                        unsigned long long* __restrict__ ccount) {
@@ -1079,30 +1097,35 @@ __global__ __launch_bounds__(256, 2) void k_kmv_mixed_sym(const uint4* __restric
   constexpr int VPER = 8 / NCH;
   __shared__ uint4 sb0[SBU], sb1[SBU];
   __shared__ float sv0[TS + 16], sv1[TS + 16];
-  __shared__ float cb0[16][TS], cb1[16][TS];   // column partials per (wave, lane group) and source
+  __shared__ float cb0[4][TS], cb1[4][TS];   // column partials per wave and source
 
   // triangle item of this block (XCD-contiguous order), column-major: column c holds r = 0 .. c, so the
   // blocks that run together on one XCD mostly share their source super-tile (L2 reuse)
-  const int64_t nitems = (int64_t)NS * (NS + 1) / 2;
+  const int64_t nitems = (int64_t)NS * (NS + 1) / 2 * (sub * sub);
   const int64_t per = (nitems + 7) / 8;
-  const int64_t item = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (item >= nitems) return;
+  const int64_t block = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (block >= nitems) return;
+  const int64_t item = block / (sub * sub);
+  const int w = (int)(block - item * (sub * sub));
   int c = (int)((sqrt(8.0 * (double)item + 1.0) - 1.0) / 2);
   if (c < 0) c = 0;
   if (c > NS - 1) c = NS - 1;
   auto col_start = [&](int64_t cc) { return cc * (cc + 1) / 2; };
   while (c > 0 && col_start(c) > item) --c;
   while (c + 1 < NS && col_start(c + 1) <= item) ++c;
-  const int r = (int)(item - col_start(c));
+  int r = (int)(item - col_start(c));
   const bool diag = r == c;
+  r = r * sub + w % sub;
+  c = c * sub + w / sub;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15;
   const int kq = lane >> 4;
-  const int64_t t0 = (int64_t)r * E, t1 = t0 + E < npad ? t0 + E : npad;
-  const int64_t s0 = (int64_t)c * E, s1 = s0 + E < npad ? s0 + E : npad;
+  const int64_t t0 = (int64_t)r * e_len, t1 = t0 + e_len < npad ? t0 + e_len : npad;
+  const int64_t s0 = (int64_t)c * e_len, s1 = s0 + e_len < npad ? s0 + e_len : npad;
+  if (t0 >= npad || s0 >= npad) return;   // a part past the last super-tile's points
   const int ntile = (int)((s1 - s0) / TS);
   constexpr float kZero = 0.0f;
 
@@ -1152,48 +1175,54 @@ __global__ __launch_bounds__(256, 2) void k_kmv_mixed_sym(const uint4* __restric
     for (int ch = 0; ch < NCH; ++ch) q0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][ch], b[ch], q0, 0, 0, 0);
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) q1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][ch], b[ch], q1, 0, 0, 0);
-#pragma unroll 2
-    for (int st = 0; st < SPT; ++st) {
-      const int rn = (st + 1) * 16 + r16;
+    float cg[4];   // column partials of four steps
+#pragma unroll 1
+    for (int s4 = 0; s4 < SPT; s4 += 4) {
 #pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) bn[ch] = __builtin_bit_cast(bf16x8, sb[rn * RS + ch * 4 + kq]);
-      const float vn = sv[rn];
-      float cs = 0.f;   // one chain over the NF x 4 targets (dependent FMAs issue back to back)
-      const bool skip = SKIP && ((sk >> st) & 1u);
+      for (int s = 0; s < 4; ++s) {
+        const int st = s4 + s;
+        const int rn = (st + 1) * 16 + r16;
 #pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        f32x4 q2 = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (f + 2 < NF) {
+        for (int ch = 0; ch < NCH; ++ch) bn[ch] = __builtin_bit_cast(bf16x8, sb[rn * RS + ch * 4 + kq]);
+        const float vn = sv[rn];
+        float cs = 0.f;   // one chain over the NF x 4 targets (dependent FMAs issue back to back)
+        const bool skip = SKIP && ((sk >> st) & 1u);
 #pragma unroll
-          for (int ch = 0; ch < NCH; ++ch)
-            q2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[f + 2 < NF ? f + 2 : 0][ch], b[ch], q2, 0, 0, 0);
-        } else {
+        for (int f = 0; f < NF; ++f) {
+          f32x4 q2 = f32x4{0.f, 0.f, 0.f, 0.f};
+          if (f + 2 < NF) {
 #pragma unroll
-          for (int ch = 0; ch < NCH; ++ch)
-            q2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[f + 2 - NF >= 0 ? f + 2 - NF : 0][ch], bn[ch], q2, 0,
-                                                         0, 0);
-        }
-        if (!skip) {
+            for (int ch = 0; ch < NCH; ++ch)
+              q2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[f + 2 < NF ? f + 2 : 0][ch], b[ch], q2, 0, 0, 0);
+          } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float ex = __builtin_amdgcn_exp2f(q0[e]);
-            a32[f][e] = __builtin_fmaf(ex, vj, a32[f][e]);
-            if (COL) cs = __builtin_fmaf(ex, vt[f][e], cs);
+            for (int ch = 0; ch < NCH; ++ch)
+              q2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[f + 2 - NF >= 0 ? f + 2 - NF : 0][ch], bn[ch], q2, 0,
+                                                           0, 0);
           }
-        }
-        q0 = q1;
-        q1 = q2;
+          if (!skip) {
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, COL ? VPER + 4 / NCH : VPER, 0);
+            for (int e = 0; e < 4; ++e) {
+              const float ex = __builtin_amdgcn_exp2f(q0[e]);
+              a32[f][e] = __builtin_fmaf(ex, vj, a32[f][e]);
+              if (COL) cs = __builtin_fmaf(ex, vt[f][e], cs);
+            }
+          }
+          q0 = q1;
+          q1 = q2;
+#pragma unroll
+          for (int ch = 0; ch < NCH; ++ch) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, COL ? VPER + 4 / NCH : VPER, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        cg[s] = cs;
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) b[ch] = bn[ch];
+        vj = vn;
       }
-      if (COL) cb[wave * 4 + kq][st * 16 + r16] = cs;
-#pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) b[ch] = bn[ch];
-      vj = vn;
+      if (COL) cb[wave][s4 * 16 + lane] = four_steps(cg);
     }
   };
 
@@ -1255,7 +1284,7 @@ __global__ __launch_bounds__(256, 2) void k_kmv_mixed_sym(const uint4* __restric
         if (COL) {
           float (*cb)[TS] = odd ? cb1 : cb0;
 #pragma unroll
-          for (int st = 0; st < SPT; ++st) cb[wave * 4 + kq][st * 16 + r16] = 0.0f;
+          for (int st = 0; st < SPT; st += 4) cb[wave][st * 16 + lane] = 0.0f;
         }
       } else {
         compute(odd ? sb1 : sb0, odd ? sv1 : sv0, odd ? cb1 : cb0, colflag, std::true_type{}, sk);
@@ -1274,11 +1303,7 @@ __global__ __launch_bounds__(256, 2) void k_kmv_mixed_sym(const uint4* __restric
       __syncthreads();
       if (COL && tid < TS) {
         float (*cb)[TS] = odd ? cb1 : cb0;
-        float h[8];
-#pragma unroll
-        for (int g = 0; g < 8; ++g) h[g] = cb[2 * g][tid] + cb[2 * g + 1][tid];
-        const float cs = ((h[0] + h[1]) + (h[2] + h[3])) + ((h[4] + h[5]) + (h[6] + h[7]));
-        *dst = prev + (double)cs;
+        *dst = prev + (double)((cb[0][tid] + cb[1][tid]) + (cb[2][tid] + cb[3][tid]));
       }
       if (t == ntile - 1) {   // row sums of this target tile -> part[c][rows]
         double* prow = part + (int64_t)c * npad + row0 + kq * 4;

@@ -80,11 +80,11 @@ static void gos(const KmvGrid& g, const uint16_t* A, const uint16_t* B, const fl
   const int64_t ngs = g.mpad / 256;
   if (cmask)
     hipLaunchKernelGGL((k_kmv_mixed_sym<NCH, NF, true>), g.grid, dim3(256), 0, s, reinterpret_cast<const uint4*>(A),
-                       reinterpret_cast<const uint4*>(B), v, g.Rp, g.E, g.NS, g.mpad, part, g.Rout, cmask, ngs,
+                       reinterpret_cast<const uint4*>(B), v, g.Rp, g.E / g.sub, g.sub, g.NS, g.mpad, part, g.Rout, cmask, ngs,
                        cull_counters());
   else
     hipLaunchKernelGGL((k_kmv_mixed_sym<NCH, NF, false>), g.grid, dim3(256), 0, s, reinterpret_cast<const uint4*>(A),
-                       reinterpret_cast<const uint4*>(B), v, g.Rp, g.E, g.NS, g.mpad, part, g.Rout, nullptr, ngs,
+                       reinterpret_cast<const uint4*>(B), v, g.Rp, g.E / g.sub, g.sub, g.NS, g.mpad, part, g.Rout, nullptr, ngs,
                        nullptr);
 }
 

@@ -80,3 +80,10 @@ def test_scan_finds_one_bad_value(gpu_lib, n, at, prec, d):
                                None, 0, 0 if prec == "fp64" else 2, U.data_ptr(), 0)
         assert rc == -1 and name.encode() in lib.krr_last_error()
         assert bool((U == 7.0).all())
+
+
+# mixed, same points: super-tiles of 1024 shared by four blocks, whole and cut off at every part (512 points, 64 padding)
+@pytest.mark.parametrize("n", [1, 511, 513, 1025, 3071, 3073, 9217])
+@pytest.mark.parametrize("d", [2, 9, 16])
+def test_same_points_mixed_parts(gpu_lib, n, d):
+    _check(gpu_lib, n, n, d, 1, 0, prec="mixed", same=True, shift=0.1)
