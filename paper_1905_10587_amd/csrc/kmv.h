@@ -39,6 +39,7 @@ struct Staged {
   mutable int cull_nf = 0;
 };
 
+constexpr int kDotRows = 64;
 constexpr int kRowPad = 1024;   // targets/sources are padded to multiples of this
 constexpr int kPrefetchRows = 32;   // extra allocated rows after the padded sources (prefetch reads)
 
@@ -122,7 +123,8 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv,
                 const double* shift_host, const double* Vraw, int prec, double* U, int64_t ldu,
                 hipStream_t s, int variant = -1, DevBuf<double>* ws = nullptr,
                 const hipEvent_t* kev = nullptr,   // kev: two events recorded around the main kernel
-                int split_req = 0);
+                int split_req = 0,
+                double* dot = nullptr);   // one K column: dot[b] = sum of Vraw[i] U[i] over staged rows kDotRows b ..
 
 // Launch table entry and the record of the last launch on this thread.
 struct KmvChoice {

@@ -336,6 +336,41 @@ __global__ void k_kmv_finish(const double* __restrict__ part, int S, int64_t mpa
   U[oi * ldu + col] = acc;
 }
 
+// The same for one K column with dense partials: 64 rows to a block, a fourth of the slots to a wave (one wave to 64 rows
+// leaves too few loads in flight: 27 us for 98 slots of 100000 rows, now 13; bound by HBM, 78 MB).  DOT: dot[b] = sum
+// over block b's rows of Vraw[i] U[i].
+constexpr int kFinishRows = kDotRows;
+template <bool DOT>
+__global__ __launch_bounds__(256) void k_kmv_finish_one(const double* __restrict__ part, int S, int64_t mpad, int64_t m,
+                                                        double shift, int has_shift, const double* __restrict__ Vraw,
+                                                        const int64_t* __restrict__ perm, double* __restrict__ U,
+                                                        int64_t ldu, double* __restrict__ dot) {
+  __shared__ double sum[3][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * kFinishRows + lane;
+  double acc = 0.0;
+  if (i < m) {
+#pragma unroll 8
+    for (int p = w; p < S; p += 4) acc += part[(int64_t)p * mpad + i];
+  }
+  if (w) sum[w - 1][lane] = acc;
+  __syncthreads();
+  if (w) return;
+  double pq = 0.0;
+  if (i < m) {
+    acc = ((acc + sum[0][lane]) + sum[1][lane]) + sum[2][lane];
+    const int64_t oi = perm ? perm[i] : i;   // staged row i is the caller's row oi
+    const double v = DOT || has_shift ? Vraw[oi] : 0.0;
+    if (has_shift) acc += shift * v;
+    U[oi * ldu] = acc;
+    pq = v * acc;
+  }
+  if (DOT) {
+    for (int o = 32; o > 0; o >>= 1) pq += __shfl_xor(pq, o);
+    if (lane == 0) dot[blockIdx.x] = pq;
+  }
+}
+
 // ------------------------------------------------------------------ variants and launcher
 namespace {
 std::mutex g_mu;
@@ -642,7 +677,7 @@ bool kernel_times_matrix_f64(const double* Xt, int64_t m, const double* Xs, int6
 
 void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const double* shift_host,
                 const double* Vraw, int prec, double* U, int64_t ldu, hipStream_t s, int variant,
-                DevBuf<double>* ws, const hipEvent_t* kev, int split_req) {
+                DevBuf<double>* ws, const hipEvent_t* kev, int split_req, double* dot) {
   KRR_REQUIRE(T.prec == prec && S.prec == prec, "staged precision mismatch");
   KRR_REQUIRE(!V.cols || (deriv == 0 && ldu >= V.ldv), "internal: a column subset is for one K product into U");
   const int R = V.Rreal, Rp = V.R;
@@ -824,7 +859,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
       if ((double)ns * T.npad * 8.0 > 2.2e9 && E != 16384) continue;
       const int64_t items = ns * (ns + 1) / 2;
       const double cost = (double)std::max<int64_t>(ceil_div(items, cus), 2) *
-                          ((double)E * (double)E + (prec == KRR_FP64 ? 30000.0 : 0.0));
+                          ((double)E * (double)E + (prec == KRR_FP64 ? 12000.0 : 0.0));
       if (cost < bestc * (1 - 1e-9)) { bestc = cost; bestE = E; }
     }
     // a requested edge: one of the candidates, a multiple of the target tile, partials near 2 GB at most
@@ -862,6 +897,19 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
   KRR_REQUIRE(ok, "kernel variant not instantiated for this shape");
   KRR_LAUNCH_CHECK();
   const int has_shift = shift_host != nullptr;
+  KRR_REQUIRE(!dot || (R == 1 && deriv == 0 && RoutK == 1 && !V.cols), "internal: p^T q is for one column");
+  if (R == 1 && deriv == 0 && RoutK == 1 && !V.cols) {
+    const dim3 grid((unsigned)ceil_div(T.n, kFinishRows));
+    const double sh = has_shift ? shift_host[0] : 0.0;
+    if (dot)
+      hipLaunchKernelGGL(k_kmv_finish_one<true>, grid, dim3(256), 0, s, (const double*)part.p, (int)split, T.npad, T.n,
+                         sh, has_shift, Vraw, (const int64_t*)T.perm.p, U, ldu, dot);
+    else
+      hipLaunchKernelGGL(k_kmv_finish_one<false>, grid, dim3(256), 0, s, (const double*)part.p, (int)split, T.npad, T.n,
+                         sh, has_shift, Vraw, (const int64_t*)T.perm.p, U, ldu, dot);
+    KRR_LAUNCH_CHECK();
+    return;
+  }
   const int Rcols = deriv == 2 ? 2 * R : R;
   const int64_t tot = T.n * Rcols;
   auto finish = [&](auto sh) {

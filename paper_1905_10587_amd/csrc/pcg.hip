@@ -23,6 +23,8 @@
 
 #include "kmv.h"
 #include "pcg.h"
+#include "pcg_fused.h"
+#include "pcg_step.h"
 #include "precond.h"
 
 namespace krr {
@@ -34,20 +36,6 @@ void validate_prec(int32_t prec);
 // Block: 256 threads = CB columns x (256/CB) rows.  Deterministic two-stage sum:
 // part[by * R + c] over row groups, then a fixed-order sum over by.
 constexpr int kRedBlocks = 256;
-
-// Halt gate of the graph-captured cycles.  *halt is 0, or u + 1 once the status of the cycle's iteration u
-// has asked the host for a decision (a convergence claim or a breakdown); a gated kernel of stage `stage`
-// does nothing when a status of an earlier stage has halted the cycle (kernels of iteration u up to its
-// status have stage u + 1, the direction update after it u + 2).  halt == nullptr: never closed.
-struct Gate {
-  const int* halt = nullptr;
-  int stage = 0;
-  __device__ bool closed() const {
-    if (!halt) return false;
-    const int h = __hip_atomic_load(halt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return h != 0 && h < stage;
-  }
-};
 
 template <int MODE>   // 0: sum a*b ; 1: sum a*a
 __global__ __launch_bounds__(256) void k_coldot(const double* __restrict__ a, const double* __restrict__ b,
@@ -104,70 +92,6 @@ __global__ __launch_bounds__(256) void k_axpy2_rr(double* __restrict__ x, double
     __syncthreads();
   }
   if (rl == 0 && c < R) part[(int64_t)blockIdx.y * R + c] = red[threadIdx.x];
-}
-
-// Scalar work done by the final reduction kernel on the column's sum v (saves a launch per scalar step):
-//   kGamma:  gamma_c = rho_c / v for active columns (0 otherwise), breakdown flag if v <= 0 or not finite;
-//   kBeta:   beta_c = v / rho_c for active columns (0 otherwise; v is the new r^T z);
-//   kStatus: the status of iteration it for the host, stored into host-mapped memory,
-//            hs = [rr = v (R) | gamma (R) | beta of the previous iteration (R) | claim (R) | flags (2)],
-//            claim_c = 1 when column c is active, it >= next_check_c and sqrt(v) / ||y_c|| <= tol (its
-//            recursive residual claims convergence); a claim or the breakdown flag closes the halt gate
-//            (when there is one) at this kernel's stage;
-//   kCheck:  the squared true residual norms of a check, also stored into hs (R).
-// it = *it_base + it_off (it_base may be null: it = it_off).
-struct DotEpilogue {
-  enum Mode { kNone = 0, kGamma = 1, kBeta = 2, kStatus = 3, kCheck = 4 };
-  int mode = kNone;
-  const double* rho = nullptr;
-  const int* active = nullptr;
-  double* gamma = nullptr;
-  double* beta = nullptr;
-  int* flags = nullptr;
-  double* hs = nullptr;
-  const int* next_check = nullptr;
-  const double* ynorm = nullptr;
-  double tol = 0.0;
-  const int* it_base = nullptr;
-  int it_off = 0;
-  int* halt = nullptr;
-};
-
-// The epilogue of column c's sum v (thread-level; out[c] = v first).  Returns gamma_c (kGamma) or beta_c
-// (kBeta), 0 otherwise.
-__device__ __forceinline__ double dot_epilogue(const DotEpilogue& e, const Gate& gate, int c, int R, double v,
-                                               double* __restrict__ out) {
-  out[c] = v;
-  if (e.mode == DotEpilogue::kGamma) {
-    double g = 0.0;
-    if (e.active[c]) {
-      if (!(v > 0.0) || !isfinite(v)) atomicOr(e.flags, 1);
-      else g = e.rho[c] / v;
-    }
-    e.gamma[c] = g;
-    return g;
-  } else if (e.mode == DotEpilogue::kBeta) {
-    double b = 0.0;
-    if (e.active[c]) b = e.rho[c] != 0.0 ? v / e.rho[c] : 0.0;
-    e.beta[c] = b;
-    return b;
-  } else if (e.mode == DotEpilogue::kStatus) {
-    const int it = (e.it_base ? *e.it_base : 0) + e.it_off;
-    const bool claim = e.active[c] && it >= e.next_check[c] && sqrt(v) / e.ynorm[c] <= e.tol;
-    e.hs[c] = v;
-    e.hs[R + c] = e.gamma[c];
-    e.hs[2 * R + c] = e.beta[c];
-    e.hs[3 * R + c] = claim ? 1.0 : 0.0;
-    const int broke = c == 0 ? __hip_atomic_load(e.flags + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-    if (c == 0) {
-      e.hs[4 * R] = (double)e.flags[0];
-      e.hs[4 * R + 1] = (double)broke;
-    }
-    if (e.halt && (claim || broke)) __hip_atomic_store(e.halt, gate.stage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } else if (e.mode == DotEpilogue::kCheck) {
-    e.hs[c] = v;
-  }
-  return 0.0;
 }
 
 // out[c] = sum_by part[by, c]: one block per column, fixed-order LDS tree (nby <= 256), then the epilogue.
@@ -487,12 +411,14 @@ struct Operator {
   }
   // out = (K + diag(shift)) v   (shift may be null).  cols (device, ncols entries): only those columns of v are
   // multiplied, into the same columns of out (shift then holds their ncols shifts); the others are not written.
+  // staged: V already holds v.  dot (one column): partial sums of v^T out, one per kDotRows rows.
   void apply(const double* v, const double* shift, double* out, hipStream_t s, const hipEvent_t* kev = nullptr,
-             const int* cols = nullptr, int ncols = 0) {
+             const int* cols = nullptr, int ncols = 0, bool staged = false, double* dot = nullptr) {
     const bool block = kmv_uses_block(prec, S.d, cols ? ncols : R, 0);
-    if (cols) stage_vectors(V, v, n, S.npad, ncols, prec, s, block, nullptr, cols, R);
+    if (staged) KRR_REQUIRE(R == 1 && V.R == 1 && !block, "internal: only one column is staged ahead");
+    else if (cols) stage_vectors(V, v, n, S.npad, ncols, prec, s, block, nullptr, cols, R);
     else stage_vectors(V, v, n, S.npad, R, prec, s, block, S.perm.p);
-    kmv_launch(S, S, V, 0, shift, v, prec, out, R, s, -1, &ws, kev);
+    kmv_launch(S, S, V, 0, shift, v, prec, out, R, s, -1, &ws, kev, 0, dot);
   }
 };
 
@@ -568,6 +494,11 @@ PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double*
   int* next_check_d = ictl.p + 2;
   ColReducer red;
   red.init(R, s);
+  // One preconditioned column: the kernels of an iteration's vector work take each other's passes over (both drivers)
+  const bool fused = P && P->kept > 0 && R == 1 && n <= kFusedRows;
+  FusedIteration fi;
+  if (fused) fi.init(*P, bidx[0], prec != KRR_FP64, n, s);
+  const double* staged = nullptr;   // the vector that Aw.V holds staged, if any
   std::vector<int> act(R, 1);
   std::vector<double> h(3 * (size_t)R);
   EventTimer tm(timing, s);
@@ -615,7 +546,10 @@ PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double*
   };
   // out = (K + diag(beta)) v with operator A over the active columns
   auto product = [&](Operator& A, const double* v, double* out, hipStream_t st, const hipEvent_t* kev) {
-    A.apply(v, colsp ? ashift.data() : betas, out, st, kev, colsp, ncols);
+    const bool ready = &A == &Aw && staged == v;
+    A.apply(v, colsp ? ashift.data() : betas, out, st, kev, colsp, ncols, ready,
+            fused && &A == &Aw ? fi.pq_part.p : nullptr);
+    if (&A == &Aw && !ready) staged = nullptr;
   };
   KRR_CHECK_HIP(hipMemcpyAsync(ynorm_d, ynorm.data(), sizeof(double) * R, hipMemcpyHostToDevice, s));
   upload_state();
@@ -809,9 +743,14 @@ PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double*
   const bool small = (int64_t)n * R <= kSmallElems;
   int CBs = 1;
   while (CBs * 2 <= R && CBs < 64) CBs *= 2;
-  // one iteration's update after its product q = A p: gamma, x += gamma p, r -= gamma q, and its status
-  auto step = [&](hipStream_t st, const DotEpilogue& es, Gate gate) {
-    if (small) {
+  // one iteration's update after its product q = A p: gamma, x += gamma p, r -= gamma q, and its status (next: the
+  // direction that follows at once; fused, the pass over r for it is taken along)
+  auto step = [&](hipStream_t st, const DotEpilogue& es, Gate gate, bool next) {
+    if (fused) {
+      if (next) tm.start(&res.st.t_precond_ms);
+      fi.step(x, r.p, pp, qq, pq, rr, epi_gamma(rho), es, next, gate, st);
+      if (next) tm.stop();
+    } else if (small) {
       hipLaunchKernelGGL(k_step_small, dim3(1), dim3(kSmallThreads), 0, st, x, r.p, (const double*)pp,
                          (const double*)qq, n, R, CBs, pq, rr, epi_gamma(rho), es, gate);
       KRR_LAUNCH_CHECK();
@@ -820,8 +759,16 @@ PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double*
       red.axpy2_rr(x, r.p, pp, qq, gamma, n, rr, st, es, gate);
     }
   };
-  // z = M^{-1} r, rho_new = r^T z, beta = rho_new / rho, pout = z + beta pin (pin for inactive columns)
-  auto direction = [&](hipStream_t st, double* pin, double* pout, Gate gate) {
+  // z = M^{-1} r, rho_new = r^T z, beta = rho_new / rho, pout = z + beta pin (pin for inactive columns); after_step: the
+  // step before took the pass over r along
+  auto direction = [&](hipStream_t st, double* pin, double* pout, Gate gate, bool after_step) {
+    if (fused) {
+      tm.start(&res.st.t_precond_ms);
+      fi.direction(r.p, z.p, pin, pout, rho_new, epi_beta(rho), after_step, Aw.V, Aw.S.perm.p, gate, st);
+      tm.stop();
+      staged = pout;
+      return;
+    }
     precondition(r.p, z.p, st);
     if (small) {
       hipLaunchKernelGGL(k_dir_small, dim3(1), dim3(kSmallThreads), 0, st, (const double*)r.p, (const double*)z.p,
@@ -839,8 +786,8 @@ PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double*
   // the step (do_step, with its status es) and then the next direction pout = z + beta pin (do_dir)
   auto step_dir = [&](hipStream_t st, bool do_step, const DotEpilogue& es, Gate gstep, bool do_dir, double* pin,
                       double* pout, Gate gdir) {
-    if (do_step) step(st, es, gstep);
-    if (do_dir) direction(st, pin, pout, gdir);
+    if (do_step) step(st, es, gstep, do_dir);
+    if (do_dir) direction(st, pin, pout, gdir, do_step);
   };
   // the next direction after a decision, in place
   auto enqueue_direction = [&](hipStream_t st, Gate gate) {
@@ -918,6 +865,7 @@ PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double*
       rho_new = rho_new0;
       throw;
     }
+    staged = nullptr;   // (a cycle begins with a direction; what it leaves staged is not relied on)
     rho = rho0;   // the capture only recorded the launches; the host's pointers advance when a cycle runs
     rho_new = rho_new0;
     KRR_CHECK_HIP(hipStreamEndCapture(cs, &graph));
@@ -947,6 +895,7 @@ PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double*
       hctrl[0] = (double)it;
       hctrl[1] = 0.0;
       KRR_CHECK_HIP(hipGraphLaunch(exec, s));
+      staged = nullptr;
       KRR_CHECK_HIP(hipEventRecord(ev_status, s));
       KRR_CHECK_HIP(hipEventSynchronize(ev_status));
       res.st.n_graph_cycles++;
@@ -1004,11 +953,11 @@ PcgResult pcg_solve(const double* X, int64_t n, int d, double eps, const double*
     const bool scheduled = replace_every > 0 && it % replace_every == 0;
     const bool handover = graph_on && it % B == 0;   // a cycle may start after this iteration
     const bool ahead = !scheduled && !handover && it < maxit;
-    step(s, epi_status(hs, nullptr, it, nullptr), Gate());
+    step(s, epi_status(hs, nullptr, it, nullptr), Gate(), ahead);
     KRR_CHECK_HIP(hipEventRecord(ev_status, s));
     const size_t tmark = tm.marks();
     if (ahead) {
-      direction(s, pp, pa, Gate());
+      direction(s, pp, pa, Gate(), true);
       tm.start(&res.st.t_mvm_ms);
       product(Aw, pa, qa, s, tm.external(&res.st.t_mvm_kernel_ms));
       tm.stop();

@@ -47,4 +47,8 @@ struct WoodburyWork {
 void woodbury_apply(const krr_precond& P, const double* x, WoodburyWork& w, bool use32, double* out,
                     hipStream_t s);
 
+// Its parts: rows per block of the pass W^T x, and z = G t.
+int woodbury_rows(int64_t n);
+void woodbury_gemv(const double* G, int kept, const double* t, double* z, hipStream_t s);
+
 }  // namespace krr

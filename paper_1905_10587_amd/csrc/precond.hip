@@ -64,7 +64,7 @@ constexpr int kWRows = 256;   // rows per block in the W^T x pass (at most)
 
 // Rows per block of the W^T x pass: kWRows, fewer for small n so that the pass still has a few hundred blocks
 // (a multiple of 4, at least 16).
-static int wt_rows(int64_t n) {
+int woodbury_rows(int64_t n) {
   return (int)std::min<int64_t>(kWRows, std::max<int64_t>(16, round_up(ceil_div(n, 256), 4)));
 }
 
@@ -115,6 +115,10 @@ __global__ __launch_bounds__(256) void k_sym_gemv(const double* __restrict__ G, 
   for (int c = lane; c < kept; c += 64) s = __builtin_fma(G[(int64_t)i * kept + c], t[c], s);
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   if (lane == 0) z[i] = s;
+}
+
+void woodbury_gemv(const double* G, int kept, const double* t, double* z, hipStream_t s) {
+  hipLaunchKernelGGL(k_sym_gemv, dim3(nblk(kept, 4)), dim3(256), 0, s, G, kept, t, z);
 }
 
 // out[i] = (x[i] - sum_c W[i, c] z[c]) / beta; a wave takes RW rows at a time (their loads in flight
@@ -168,7 +172,7 @@ int beta_index(const krr_precond& P, double beta) {
 }
 
 // One column of Algorithm 4 with caller-provided buffers: x and out are columns of n x R row-major blocks
-// (strides ldx, ldo); partial holds ceil(n / wt_rows(n)) x kept doubles (at most max(256, ceil(n / 256)) x kept),
+// (strides ldx, ldo); partial holds ceil(n / woodbury_rows(n)) x kept doubles (at most max(256, ceil(n / 256)) x kept),
 // t and z kept doubles each.  Every slot of
 // partial is written before it is read, so the buffers need no clearing.
 static void woodbury_one_column(const krr_precond& P, const double* x, int ldx, int b, bool use32, double* out,
@@ -176,7 +180,7 @@ static void woodbury_one_column(const krr_precond& P, const double* x, int ldx, 
   const int kept = P.kept;
   const int64_t n = P.n;
   const double* G = use32 ? P.G32[b].p : P.G64[b].p;
-  const int rows = wt_rows(n);
+  const int rows = woodbury_rows(n);
   const int nb = (int)ceil_div(n, rows);
   const dim3 gw((unsigned)nb, nblk(kept));
   if (use32)
@@ -184,7 +188,7 @@ static void woodbury_one_column(const krr_precond& P, const double* x, int ldx, 
   else
     hipLaunchKernelGGL(k_wt_partial<double>, gw, dim3(256), 0, s, P.W64.p, n, kept, x, ldx, rows, partial);
   hipLaunchKernelGGL(k_reduce_partials, dim3((unsigned)kept), dim3(256), 0, s, partial, nb, kept, t);
-  hipLaunchKernelGGL(k_sym_gemv, dim3(nblk(kept, 4)), dim3(256), 0, s, G, kept, t, z);
+  woodbury_gemv(G, kept, t, z, s);
   // two rows per wave and at most 2048 blocks (measured best among 1, 2, 4 rows and 1024-8192 blocks)
   const unsigned g = (unsigned)std::min<int64_t>(ceil_div(n, 8), 2048);
   const size_t lds = (size_t)kept * sizeof(double);
@@ -199,7 +203,7 @@ static void woodbury_one_column(const krr_precond& P, const double* x, int ldx, 
 
 // Doubles of scratch one column of woodbury_one_column needs.
 static int64_t woodbury_column_scratch(const krr_precond& P) {
-  return ceil_div(P.n, wt_rows(P.n)) * (int64_t)P.kept + 2 * (int64_t)P.kept;
+  return ceil_div(P.n, woodbury_rows(P.n)) * (int64_t)P.kept + 2 * (int64_t)P.kept;
 }
 
 void WoodburyWork::prepare(const krr_precond& P, int R_, const int* bidx_host_, hipStream_t s) {
@@ -207,7 +211,7 @@ void WoodburyWork::prepare(const krr_precond& P, int R_, const int* bidx_host_, 
   bidx_host.assign(bidx_host_, bidx_host_ + R);
   const int kept = P.kept;
   if (R == 1) {
-    partial.alloc((size_t)ceil_div(P.n, wt_rows(P.n)) * kept, s);
+    partial.alloc((size_t)ceil_div(P.n, woodbury_rows(P.n)) * kept, s);
     t.alloc(kept, s);
     z.alloc(kept, s);
     return;
@@ -681,7 +685,7 @@ extern "C" int krr_precond_apply_noalloc(const krr_precond* P, const double* x, 
                     std::to_string(krr::noalloc_scratch_bytes()) + " bytes");
     double* base = static_cast<double*>(krr::noalloc_scratch());
     double* partial = base;
-    double* t = partial + krr::ceil_div(P->n, krr::wt_rows(P->n)) * P->kept;
+    double* t = partial + krr::ceil_div(P->n, krr::woodbury_rows(P->n)) * P->kept;
     double* z = t + P->kept;
     hipStream_t s = (hipStream_t)stream;
     for (int r = 0; r < R; ++r) krr::woodbury_one_column(*P, x + r, R, bidx[r], use32, out + r, R, partial, t, z, s);
