@@ -47,6 +47,11 @@ struct WoodburyWork {
 void woodbury_apply(const krr_precond& P, const double* x, WoodburyWork& w, bool use32, double* out,
                     hipStream_t s);
 
+// The apply of 2 .. kBlockColumns columns (woodbury_block.hip), prepared by WoodburyWork::prepare.
+constexpr int kBlockColumns = 16;
+void woodbury_block_prepare(const krr_precond& P, WoodburyWork& w, hipStream_t s);
+void woodbury_block_apply(const krr_precond& P, const double* X, WoodburyWork& w, bool use32, double* out, hipStream_t s);
+
 // Its parts: rows per block of the pass W^T x, and z = G t.
 int woodbury_rows(int64_t n);
 void woodbury_gemv(const double* G, int kept, const double* t, double* z, hipStream_t s);

@@ -226,6 +226,10 @@ void WoodburyWork::prepare(const krr_precond& P, int R_, const int* bidx_host_, 
   KRR_CHECK_HIP(hipMemcpyAsync(invb.p, ib.data(), sizeof(double) * R, hipMemcpyHostToDevice, s));
   KRR_CHECK_HIP(hipMemcpyAsync(bidx.p, bidx_host.data(), sizeof(int) * R, hipMemcpyHostToDevice, s));
   KRR_CHECK_HIP(hipStreamSynchronize(s));   // the host vectors above are temporaries
+  if (R <= kBlockColumns) {
+    woodbury_block_prepare(P, *this, s);
+    return;
+  }
   T.alloc((size_t)kept * R, s);
   Zall.alloc((size_t)nbeta * kept * R, s);
   Z.alloc((size_t)kept * R, s);
@@ -239,6 +243,10 @@ void woodbury_apply(const krr_precond& P, const double* x, WoodburyWork& w, bool
   KRR_REQUIRE(!use32 || P.W32.p, "preconditioner was built without an FP32 factor");
   if (R == 1) {
     woodbury_one_column(P, x, 1, w.bidx_host[0], use32, out, 1, w.partial.p, w.t.p, w.z.p, s);
+    return;
+  }
+  if (R <= kBlockColumns) {
+    woodbury_block_apply(P, x, w, use32, out, s);
     return;
   }
   // Block form (FP64 matrix cores; the FP32 factor's products are exact in FP64): T = W^T X, summed over row
