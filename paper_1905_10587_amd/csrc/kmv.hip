@@ -691,6 +691,11 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
   }
   if (variant < 0) variant = kmv_default_variant(prec, T.d, R, T.n, S.n, &T == &S && deriv == 0);
   KRR_REQUIRE(variant < kmv_num_variants(prec, R), "unknown kernel variant");
+  // A variant of the many-column class names a block kernel; products that have none (derivatives, more than 20
+  // coordinates) take the direct form of that number, or of one column where there is none.
+  if (prec != KRR_FP64 && rclass(prec, R) == 3 && !kmv_uses_block(prec, T.d, R, deriv) &&
+      variant >= (prec == KRR_MIXED ? 10 : 3))
+    variant = kmv_default_variant(prec, T.d, 1, T.n, S.n, false);
   int64_t rows;
   int gz, TM = 1, NF = 1, RC = R == 1 ? 1 : R <= 4 ? 4 : 8;
   int form = 0;   // mixed single-column kernel form

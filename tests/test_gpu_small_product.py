@@ -87,3 +87,10 @@ def test_scan_finds_one_bad_value(gpu_lib, n, at, prec, d):
 @pytest.mark.parametrize("d", [2, 9, 16])
 def test_same_points_mixed_parts(gpu_lib, n, d):
     _check(gpu_lib, n, n, d, 1, 0, prec="mixed", same=True, shift=0.1)
+
+
+# many 32-bit columns without a block kernel: derivatives, and more than 20 coordinates
+@pytest.mark.parametrize("prec", ["fp32", "mixed"])
+@pytest.mark.parametrize("n,d,R,deriv", [(918, 54, 64, 0), (300, 33, 9, 0), (1100, 6, 33, 2), (257, 3, 9, 1), (130, 20, 40, 2)])
+def test_many_columns_without_a_block_kernel(gpu_lib, prec, n, d, R, deriv):
+    _check(gpu_lib, n, n, d, R, deriv, prec=prec, same=True)
