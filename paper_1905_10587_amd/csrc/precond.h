@@ -48,7 +48,7 @@ void woodbury_apply(const krr_precond& P, const double* x, WoodburyWork& w, bool
                     hipStream_t s);
 
 // The apply of 2 .. kBlockColumns columns (woodbury_block.hip), prepared by WoodburyWork::prepare.
-constexpr int kBlockColumns = 16;
+constexpr int kBlockColumns = 256;
 void woodbury_block_prepare(const krr_precond& P, WoodburyWork& w, hipStream_t s);
 void woodbury_block_apply(const krr_precond& P, const double* X, WoodburyWork& w, bool use32, double* out, hipStream_t s);
 
