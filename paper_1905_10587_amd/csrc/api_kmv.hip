@@ -45,10 +45,12 @@ void kernel_mv_raw(const double* Xt, int64_t m, const double* Xs, int64_t n, int
   const bool sort = same && prec == KRR_MIXED && R == 1 && deriv == 0 && cull_wanted(*scan, n, d, eps);
   const bool block = kmv_uses_block(prec, d, R, deriv);
   const int parts = block ? kStageSplit : kStageDirect;
-  stage_points(S, Xs, n, d, eps, prec, scan, same, true, s, sort, parts);
-  if (!same) stage_points(T, Xt, m, d, eps, prec, scan, true, false, s, false, parts);
+  StageBatch batch;
+  stage_points(S, Xs, n, d, eps, prec, scan, same, true, s, sort, parts, &batch);
+  if (!same) stage_points(T, Xt, m, d, eps, prec, scan, true, false, s, false, parts, &batch);
   StagedVec SV;
-  stage_vectors(SV, V, n, S.npad, R, prec, s, block, S.perm.p);
+  stage_vectors(SV, V, n, S.npad, R, prec, s, block, S.perm.p, nullptr, 0, &batch);
+  batch.launch(s);
   kmv_launch(same ? S : T, S, SV, deriv, shift, V, prec, U, ldu, s);
 }
 

@@ -48,13 +48,40 @@ int padded_dim(int d);
 // Number of 32-wide K chunks of the split-BF16 cross term for dimension d.
 int mixed_chunks(int d);
 
-// Stage a point set.  ps: the scan of the operator's points; its centre is the translation of the staged copies (the
+// Staging work: jobs collected from several calls go out in one launch.
+struct StageJob {
+  enum Kind { kPoints64, kPoints32, kSplitTarget, kSplitSource, kVector };
+  int kind;
+  const double* in;   // n rows: points of d coordinates, or vectors of d columns
+  int64_t n;
+  int d, width;       // width: values per staged row
+  const double* center;
+  double scale = 0.0;
+  const int64_t* perm = nullptr;
+  const int* cols = nullptr;
+  int ldv = 0;
+  double* o64 = nullptr;
+  float* o32 = nullptr;
+  uint16_t* o16 = nullptr;
+  int64_t total = 0;  // threads
+  int first = 0;      // block
+};
+struct StageBatch {
+  static constexpr int kJobs = 6;
+  StageJob job[kJobs];
+  int count = 0, blocks = 0;
+  void add(StageJob j, int64_t threads);
+  void launch(hipStream_t s);
+};
+
+// Stage a point set (into batch, for its launch, where given).  ps: the scan of the operator's points; its centre is the translation of the staged copies (the
 // kernel is translation invariant; pass the same scan for targets and sources), nullptr: none (FP64 only).
 // sort: stage a square operator's points in spatial order with culling boxes (MIXED only; see Staged).
 // parts (FP32): which copies its products will read, the direct kernels' coordinates or the block kernels' split rows.
 enum StageParts { kStageDirect = 1, kStageSplit = 2, kStageAll = 3 };
 void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int prec, const PointScan* ps,
-                  bool as_target, bool as_source, hipStream_t s, bool sort = false, int parts = kStageAll);
+                  bool as_target, bool as_source, hipStream_t s, bool sort = false, int parts = kStageAll,
+                  StageBatch* batch = nullptr);
 
 // Exact far-tile culling of the symmetric mixed form.  A 16-source step of a wave's 16 NF targets is skipped
 // when every kernel value in it is exactly zero in FP32: the boxes' minimum scaled squared distance exceeds
@@ -99,7 +126,8 @@ bool kmv_uses_block(int prec, int d, int R, int deriv);
 // MVM then writes its products to those columns of U (one product without the derivative kernel).  block: the product
 // will take the block path (kmv_uses_block), which stages its own form; only the sizes are set.
 void stage_vectors(StagedVec& sv, const double* V, int64_t n, int64_t npad, int R, int prec, hipStream_t s,
-                   bool block, const int64_t* perm = nullptr, const int* cols = nullptr, int ldv = 0);
+                   bool block, const int64_t* perm = nullptr, const int* cols = nullptr, int ldv = 0,
+                   StageBatch* batch = nullptr);
 
 // FP64 products of few pairs from the caller's arrays (kmv_small.hip): whether (m, n, d, R, deriv, prec) is one, and
 // the product U (row stride ldu) = K or K' V (+ shift V), deriv as in kmv_launch.  U overlaps no input.  bad: nbad

@@ -45,24 +45,15 @@ int mixed_chunks(int d) {
 }
 
 // ------------------------------------------------------------------ staging kernels
-// FP64 copy, translated by center when given (the kernel is translation invariant; centred coordinates keep
-// the norms, and so the cancellation of the matrix-core form, small)
-__global__ void k_stage_f64(const double* __restrict__ X, int64_t n, int d, int64_t npad, int dpad,
-                            const double* __restrict__ center, double* __restrict__ out) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= npad * dpad) return;
-  int64_t i = idx / dpad;
-  int k = (int)(idx % dpad);
-  out[idx] = (i < n && k < d) ? X[i * d + k] - (center ? center[k] : 0.0) : 0.0;
-}
-
-__global__ void k_stage_f32(const double* __restrict__ X, int64_t n, int d, int64_t npad, int dpad,
-                            const double* __restrict__ center, double scale, float* __restrict__ out) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= npad * dpad) return;
-  int64_t i = idx / dpad;
-  int k = (int)(idx % dpad);
-  out[idx] = (i < n && k < d) ? (float)((X[i * d + k] - center[k]) * scale) : 0.0f;
+// One job of a staging launch: element idx of one staged array.  FP64 copies are translated by center when given (the
+// kernel is translation invariant; centred coordinates keep the norms, and so the cancellation of the matrix-core form,
+// small).
+__device__ __forceinline__ void stage_point(const StageJob& g, int64_t idx) {
+  const int64_t i = idx / g.width;
+  const int k = (int)(idx % g.width);
+  const bool in = i < g.n && k < g.d;
+  if (g.kind == StageJob::kPoints64) g.o64[idx] = in ? g.in[i * g.d + k] - (g.center ? g.center[k] : 0.0) : 0.0;
+  else g.o32[idx] = in ? (float)((g.in[i * g.d + k] - g.center[k]) * g.scale) : 0.0f;
 }
 
 __device__ __forceinline__ uint16_t bf16_rn(float f) {
@@ -88,13 +79,11 @@ __device__ __forceinline__ void split3(double x, uint16_t& h, uint16_t& m, uint1
 // with n = -c ||z||^2 split into three parts.  sum_k a_k b_k = -c ||z_t - z_s||^2 up to the
 // dropped m*l, l*m, l*l products (relative size below 2^-24).
 // Eight values (16 bytes) of one point's row per thread, consecutive threads consecutive bytes: a thread per row wrote
-// two bytes at a time, 128 apart (n = 1e5, d = 8: 43 us a side; now 28 for both).  grid.y: sides side0 ..
-__global__ void k_stage_split(const double* __restrict__ X, int64_t n, int d, int64_t npad, int ka,
-                              const double* __restrict__ center, double c, int side0,
-                              const int64_t* __restrict__ perm, uint16_t* __restrict__ sa, uint16_t* __restrict__ sb) {
-  const int side = side0 + blockIdx.y, per = ka / 8;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= npad * per) return;
+// two bytes at a time, 128 apart (n = 1e5, d = 8: 43 us a side; now 28 for both).
+__device__ __forceinline__ void stage_split(const StageJob& g, int64_t t) {
+  const int side = g.kind == StageJob::kSplitTarget ? 0 : 1, per = g.width / 8, d = g.d;
+  const double* center = g.center;
+  const double c = g.scale;
   const int64_t i = t / per;
   const int k0 = (int)(t % per) * 8;
   union {
@@ -102,8 +91,8 @@ __global__ void k_stage_split(const double* __restrict__ X, int64_t n, int d, in
     uint4 v;
   } o;
   o.v = uint4{0, 0, 0, 0};
-  if (i < n && k0 < 6 * d + 6) {
-    const double* x = X + (perm ? perm[i] : i) * d;   // staged point i is the caller's point perm[i]
+  if (i < g.n && k0 < 6 * d + 6) {
+    const double* x = g.in + (g.perm ? g.perm[i] : i) * d;   // staged point i is the caller's point perm[i]
     // part (0 hi, 1 mid, 2 lo) of section s in the layout above
     const unsigned parts = side == 0 ? 0x120100u : 0x102010u;   // hex digit s (from the right): sections h h m h l m / h m h l h m
     int sec = k0 / d, dim = k0 - sec * d;
@@ -131,7 +120,42 @@ __global__ void k_stage_split(const double* __restrict__ X, int64_t n, int d, in
       }
     }
   }
-  *reinterpret_cast<uint4*>((side == 0 ? sa : sb) + i * ka + k0) = o.v;
+  *reinterpret_cast<uint4*>(g.o16 + i * g.width + k0) = o.v;
+}
+
+__device__ __forceinline__ void stage_vec(const StageJob& g, int64_t idx) {
+  const int64_t i = idx / g.width;
+  const int c = (int)(idx % g.width);
+  const double v = i < g.n && c < g.d ? g.in[(g.perm ? g.perm[i] : i) * g.ldv + (g.cols ? g.cols[c] : c)] : 0.0;
+  if (g.o64) g.o64[idx] = v;
+  if (g.o32) g.o32[idx] = (float)v;
+}
+
+// The jobs one after another over the grid; a launch each (and its dependency) would cost a small call 4 us a job.
+__global__ __launch_bounds__(256) void k_stage(StageBatch b) {
+  int j = 0;
+  while (j + 1 < b.count && (int)blockIdx.x >= b.job[j + 1].first) ++j;
+  const StageJob& g = b.job[j];
+  const int64_t t = (int64_t)((int)blockIdx.x - g.first) * 256 + threadIdx.x;
+  if (t >= g.total) return;
+  if (g.kind == StageJob::kVector) stage_vec(g, t);
+  else if (g.kind == StageJob::kSplitTarget || g.kind == StageJob::kSplitSource) stage_split(g, t);
+  else stage_point(g, t);
+}
+
+void StageBatch::add(StageJob j, int64_t threads) {
+  KRR_REQUIRE(count < kJobs, "internal: too many staging jobs");
+  j.total = threads;
+  j.first = blocks;
+  blocks += (int)ceil_div(threads, 256);
+  job[count++] = j;
+}
+
+void StageBatch::launch(hipStream_t s) {
+  if (!count) return;
+  hipLaunchKernelGGL(k_stage, dim3((unsigned)blocks), dim3(256), 0, s, *this);
+  KRR_LAUNCH_CHECK();
+  count = blocks = 0;
 }
 
 void spatial_order(Staged& st, const double* X, const PointScan& ps, hipStream_t s);
@@ -145,7 +169,8 @@ static int64_t staged_rows(int64_t n, int prec, bool targets_only) {
 }
 
 void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int prec, const PointScan* ps,
-                  bool as_target, bool as_source, hipStream_t s, bool sort, int parts) {
+                  bool as_target, bool as_source, hipStream_t s, bool sort, int parts, StageBatch* batch) {
+  StageBatch own, &jobs = batch ? *batch : own;
   st.n = n;
   st.d = d;
   st.npad = staged_rows(n, prec, as_target && !as_source);
@@ -154,13 +179,12 @@ void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int
   st.eps = eps;
   KRR_REQUIRE(st.dpad > 0, "d exceeds KRR_MAX_D");
   const int64_t tot = st.npad * st.dpad;
-  const int blk = 256;
   const double* center = ps ? ps->center.p : nullptr;
   if (prec == KRR_FP64) {
     st.x64.alloc(tot, s);
-    hipLaunchKernelGGL(k_stage_f64, dim3(ceil_div(tot, blk)), dim3(blk), 0, s, X, n, d, st.npad, st.dpad, center,
-                       st.x64.p);
-    KRR_LAUNCH_CHECK();
+    StageJob j{StageJob::kPoints64, X, n, d, st.dpad, center};
+    j.o64 = st.x64.p;
+    jobs.add(j, tot);
     if (ps && as_target && as_source) {
       // the box of the points bounds every squared distance by diag2 and the staged squared norms by max2
       double diag2 = 0.0, max2 = 0.0;
@@ -176,10 +200,10 @@ void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int
     KRR_REQUIRE(center, "internal: FP32 and mixed operators are staged about a centre");
     if (prec == KRR_FP32 && (parts & kStageDirect)) {
       st.x32.alloc(tot, s);
-      const double scale = std::sqrt(kLog2e / eps);
-      hipLaunchKernelGGL(k_stage_f32, dim3(ceil_div(tot, blk)), dim3(blk), 0, s, X, n, d, st.npad, st.dpad,
-                         center, scale, st.x32.p);
-      KRR_LAUNCH_CHECK();
+      StageJob j{StageJob::kPoints32, X, n, d, st.dpad, center};
+      j.scale = std::sqrt(kLog2e / eps);
+      j.o32 = st.x32.p;
+      jobs.add(j, tot);
     }
     // split vectors: the MFMA kernels (single column for MIXED, block for MIXED and FP32)
     st.ka = 32 * mixed_chunks(d);
@@ -191,28 +215,21 @@ void stage_points(Staged& st, const double* X, int64_t n, int d, double eps, int
     if (prec == KRR_MIXED || (parts & kStageSplit)) {
       if (as_target) st.sa.alloc(st.npad * st.ka, s);
       if (as_source) st.sb.alloc((st.npad + kPrefetchRows) * st.ka, s);   // padding rows: read by the last prefetch only
-      hipLaunchKernelGGL(k_stage_split, dim3((unsigned)ceil_div(st.npad * (st.ka / 8), blk), as_target && as_source ? 2u : 1u),
-                         dim3(blk), 0, s, X, n, d, st.npad, st.ka, center, c, as_target ? 0 : 1,
-                         (const int64_t*)st.perm.p, st.sa.p, st.sb.p);
-      KRR_LAUNCH_CHECK();
+      StageJob j{StageJob::kSplitTarget, X, n, d, st.ka, center};
+      j.scale = c;
+      j.perm = st.perm.p;
+      j.o16 = st.sa.p;
+      if (as_target) jobs.add(j, st.npad * (st.ka / 8));
+      j.kind = StageJob::kSplitSource;
+      j.o16 = st.sb.p;
+      if (as_source) jobs.add(j, st.npad * (st.ka / 8));
     }
   }
-}
-
-__global__ void k_stage_vec(const double* __restrict__ V, int64_t n, int R, int64_t npad, int Rp,
-                            const int64_t* __restrict__ perm, const int* __restrict__ cols, int ldv,
-                            double* __restrict__ o64, float* __restrict__ o32) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= npad * Rp) return;
-  int64_t i = idx / Rp;
-  int c = (int)(idx % Rp);
-  double v = (i < n && c < R) ? V[(perm ? perm[i] : i) * ldv + (cols ? cols[c] : c)] : 0.0;
-  if (o64) o64[idx] = v;
-  if (o32) o32[idx] = (float)v;
+  if (!batch) own.launch(s);
 }
 
 void stage_vectors(StagedVec& sv, const double* V, int64_t n, int64_t npad, int R, int prec, hipStream_t s,
-                   bool block, const int64_t* perm, const int* cols, int ldv) {
+                   bool block, const int64_t* perm, const int* cols, int ldv, StageBatch* batch) {
   KRR_REQUIRE(!cols || (ldv >= R && !perm), "internal: a column subset needs its row stride and the caller's order");
   sv.npad = npad;
   sv.Rreal = R;
@@ -231,9 +248,15 @@ void stage_vectors(StagedVec& sv, const double* V, int64_t n, int64_t npad, int 
     if (sv.v32.n < cap) sv.v32.alloc(cap, s);
   }
   if (block) return;   // the matrix-core block path lays out its own; fewer active columns may yet leave it
-  hipLaunchKernelGGL(k_stage_vec, dim3(ceil_div(tot, 256)), dim3(256), 0, s, V, n, R, npad, sv.R, perm, cols,
-                     sv.ldv, sv.v64.p, sv.v32.p);
-  KRR_LAUNCH_CHECK();
+  StageJob j{StageJob::kVector, V, n, R, sv.R, nullptr};
+  j.perm = perm;
+  j.cols = cols;
+  j.ldv = sv.ldv;
+  j.o64 = sv.v64.p;
+  j.o32 = sv.v32.p;
+  StageBatch own, &jobs = batch ? *batch : own;
+  jobs.add(j, tot);
+  if (!batch) own.launch(s);
 }
 
 __global__ void k_stage_v4(const double* __restrict__ V, int64_t n, int R, int64_t npad, int Rb, int nsplit,
