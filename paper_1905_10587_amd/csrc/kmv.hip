@@ -838,6 +838,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
   // rounds x (per-block source count + a fixed per-block cost), so the last round is not mostly idle.
   // The block path caps its FP64 partial buffer near 2 GB.
   KmvGrid q{dim3(1, 1, 1), 0, nsrc, T.npad, RpK, RoutK};
+  q.d = T.d;
   const int64_t cap = resident_blocks(
       [&](int* occ) {
         q.occ = occ;
@@ -915,6 +916,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
     g.NS = (int)ns;
     g.sub = sub;
   }
+  g.d = T.d;
   const size_t need = (size_t)split * T.npad * RoutK;
   if (part.n < need) part.alloc(need, s);
   t_last = KmvLaunchInfo{variant, (int)(sym ? g.E : src_len), sym ? 1 : 0, cmask ? 1 : 0, T.npad, NF};

@@ -7,12 +7,18 @@ namespace krr {
 template <int D, int TM, int RC, int DV>
 static void go32(const KmvGrid& g, const float* xt, const float* xs, const float* v,
                  double* part, hipStream_t s) {
-  if (g.occ) {
-    KRR_CHECK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(g.occ, k_kmv_f32<D, TM, RC, DV>, 256, 0));
-    return;
-  }
-  hipLaunchKernelGGL((k_kmv_f32<D, TM, RC, DV>), g.grid, dim3(256), 0, s, xt, xs, v, g.Rp, g.src_len, g.n_src,
-                     part, g.mpad, g.Rout);
+  auto go = [&](auto dr) {
+    constexpr int DR = decltype(dr)::value;
+    if (g.occ) {
+      KRR_CHECK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(g.occ, k_kmv_f32<D, TM, RC, DV, DR>, 256, 0));
+      return;
+    }
+    hipLaunchKernelGGL((k_kmv_f32<D, TM, RC, DV, DR>), g.grid, dim3(256), 0, s, xt, xs, v, g.Rp, g.src_len, g.n_src,
+                       part, g.mpad, g.Rout);
+  };
+  // (eight columns hide one coordinate of six or eight: 20011 points, d = 5, 7 columns 288 us with six, 304 with five)
+  if constexpr (TM == 1 && (RC < 8 || D > 8)) with_coordinates<D>(g.d, go);
+  else go(std::integral_constant<int, D>{});
 }
 
 #define KRR_DV(D, TM, RC)                                   \

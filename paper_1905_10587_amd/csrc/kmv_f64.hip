@@ -7,12 +7,17 @@ namespace krr {
 template <int D, int TM, int RC, int DV, int TSX = 0>
 static void go64(const KmvGrid& g, const double* xt, const double* xs, const double* v, double neg_c,
                  double* part, hipStream_t s) {
-  if (g.occ) {
-    KRR_CHECK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(g.occ, k_kmv_f64<D, TM, RC, DV, TSX>, 256, 0));
-    return;
-  }
-  hipLaunchKernelGGL((k_kmv_f64<D, TM, RC, DV, TSX>), g.grid, dim3(256), 0, s, xt, xs, v, g.Rp, g.src_len,
-                     g.n_src, neg_c, part, g.mpad, g.Rout);
+  auto go = [&](auto dr) {
+    constexpr int DR = decltype(dr)::value;
+    if (g.occ) {
+      KRR_CHECK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(g.occ, k_kmv_f64<D, TM, RC, DV, TSX, DR>, 256, 0));
+      return;
+    }
+    hipLaunchKernelGGL((k_kmv_f64<D, TM, RC, DV, TSX, DR>), g.grid, dim3(256), 0, s, xt, xs, v, g.Rp, g.src_len,
+                       g.n_src, neg_c, part, g.mpad, g.Rout);
+  };
+  if constexpr (TM == 1 && RC <= 8) with_coordinates<D>(g.d, go);
+  else go(std::integral_constant<int, D>{});
 }
 
 #define KRR_DV(D, TM, RC)                                   \

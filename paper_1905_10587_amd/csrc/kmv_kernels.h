@@ -49,9 +49,10 @@ struct DirectTile {
   static constexpr int TS = D <= 16 ? 256 : (D <= 32 ? 128 : 64);
 };
 
+// DR: coordinates evaluated (of D staged; the others are zeros and add nothing).
 // TSX != 0: source tiles of TSX points (the short-split form for small products, whose source splits are
 // multiples of TSX rather than of 256).
-template <int D, int TM, int RC, int DV, int TSX = 0>
+template <int D, int TM, int RC, int DV, int TSX = 0, int DR = D>
 __global__ __launch_bounds__(256) void k_kmv_f64(const double* __restrict__ xt, const double* __restrict__ xs,
                                                  const double* __restrict__ v, int Rp, int64_t src_len,
                                                  int64_t n_src, double neg_c, double* __restrict__ part,
@@ -65,11 +66,11 @@ __global__ __launch_bounds__(256) void k_kmv_f64(const double* __restrict__ xt, 
   const int c0 = blockIdx.z * RC;
   const int64_t jb = (int64_t)blockIdx.y * src_len;
   const int64_t je = jb + src_len < n_src ? jb + src_len : n_src;
-  double xi[TM][D];
+  double xi[TM][DR];
 #pragma unroll
   for (int t = 0; t < TM; ++t)
 #pragma unroll
-    for (int k = 0; k < D; ++k) xi[t][k] = xt[(ibase + t * 256) * D + k];
+    for (int k = 0; k < DR; ++k) xi[t][k] = xt[(ibase + t * 256) * D + k];
   double acc[TM][RC][NO];
 #pragma unroll
   for (int t = 0; t < TM; ++t)
@@ -84,16 +85,16 @@ __global__ __launch_bounds__(256) void k_kmv_f64(const double* __restrict__ xt, 
     __syncthreads();
 #pragma unroll 2
     for (int j = 0; j < TS; ++j) {
-      double xj[D], vj[RC];
+      double xj[DR], vj[RC];
 #pragma unroll
-      for (int k = 0; k < D; ++k) xj[k] = sx[j * D + k];
+      for (int k = 0; k < DR; ++k) xj[k] = sx[j * D + k];
 #pragma unroll
       for (int c = 0; c < RC; ++c) vj[c] = sv[j * RC + c];
 #pragma unroll
       for (int t = 0; t < TM; ++t) {
         double d2 = 0.0;
 #pragma unroll
-        for (int k = 0; k < D; ++k) {
+        for (int k = 0; k < DR; ++k) {
           const double df = xi[t][k] - xj[k];
           d2 = __builtin_fma(df, df, d2);
         }
@@ -490,7 +491,8 @@ __global__ __launch_bounds__(256) void k_kmv_f64_symm(const double* __restrict__
 
 // FP32 form: coordinates pre-scaled so that q = -||t'-s'||^2 is the exp2 argument.  Per pair: D subs,
 // D FMAs, one v_exp_f32, RC FMAs.  FP32 partial sums are folded into FP64 once per 256 sources.
-template <int D, int TM, int RC, int DV>
+// DR: coordinates evaluated (of D staged; the others are zeros and add nothing).
+template <int D, int TM, int RC, int DV, int DR = D>
 __global__ __launch_bounds__(256) void k_kmv_f32(const float* __restrict__ xt, const float* __restrict__ xs,
                                                  const float* __restrict__ v, int Rp, int64_t src_len,
                                                  int64_t n_src, double* __restrict__ part, int64_t mpad,
@@ -503,11 +505,11 @@ __global__ __launch_bounds__(256) void k_kmv_f32(const float* __restrict__ xt, c
   const int c0 = blockIdx.z * RC;
   const int64_t jb = (int64_t)blockIdx.y * src_len;
   const int64_t je = jb + src_len < n_src ? jb + src_len : n_src;
-  float xi[TM][D];
+  float xi[TM][DR];
 #pragma unroll
   for (int t = 0; t < TM; ++t)
 #pragma unroll
-    for (int k = 0; k < D; ++k) xi[t][k] = xt[(ibase + t * 256) * D + k];
+    for (int k = 0; k < DR; ++k) xi[t][k] = xt[(ibase + t * 256) * D + k];
   double acc[TM][RC][NO];
 #pragma unroll
   for (int t = 0; t < TM; ++t)
@@ -530,16 +532,16 @@ __global__ __launch_bounds__(256) void k_kmv_f32(const float* __restrict__ xt, c
         for (int o = 0; o < NO; ++o) a32[t][c][o] = 0.0f;
 #pragma unroll 2
     for (int j = 0; j < TS; ++j) {
-      float xj[D], vj[RC];
+      float xj[DR], vj[RC];
 #pragma unroll
-      for (int k = 0; k < D; ++k) xj[k] = sx[j * D + k];
+      for (int k = 0; k < DR; ++k) xj[k] = sx[j * D + k];
 #pragma unroll
       for (int c = 0; c < RC; ++c) vj[c] = sv[j * RC + c];
 #pragma unroll
       for (int t = 0; t < TM; ++t) {
         float d2 = 0.0f;
 #pragma unroll
-        for (int k = 0; k < D; ++k) {
+        for (int k = 0; k < DR; ++k) {
           const float df = xi[t][k] - xj[k];
           d2 = __builtin_fmaf(df, df, d2);
         }

@@ -94,3 +94,11 @@ def test_same_points_mixed_parts(gpu_lib, n, d):
 @pytest.mark.parametrize("n,d,R,deriv", [(918, 54, 64, 0), (300, 33, 9, 0), (1100, 6, 33, 2), (257, 3, 9, 1), (130, 20, 40, 2)])
 def test_many_columns_without_a_block_kernel(gpu_lib, prec, n, d, R, deriv):
     _check(gpu_lib, n, n, d, R, deriv, prec=prec, same=True)
+
+
+# the direct forms' coordinate and column counts: every d up to 32 at its staged width, chunks of one to eight columns
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("d,R,deriv", [(1, 3, 0), (5, 7, 0), (7, 6, 0), (9, 1, 2), (10, 2, 0), (11, 4, 0), (12, 5, 0), (13, 8, 0),
+                                       (15, 7, 0), (17, 1, 0), (20, 3, 0), (21, 1, 2), (26, 6, 0), (27, 1, 0), (32, 7, 0)])
+def test_direct_counts(gpu_lib, prec, d, R, deriv):
+    _check(gpu_lib, 2100, 4200, d, R, deriv, prec=prec)
