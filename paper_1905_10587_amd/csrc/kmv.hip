@@ -797,7 +797,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
       TM = 1;
     }
     while (!sym && T.npad % (256 * TM)) TM /= 2;   // few targets are staged in whole blocks of a smaller tile
-    rows = f64sm ? 64 * NF : 256 * TM;
+    rows = f64sm ? 64 * NF : prec == KRR_FP64 && D > 32 ? 64 : 256 * TM;
     gz = (int)ceil_div(R, RC);   // real columns only (Rp is padded to 8)
     KRR_REQUIRE(Rp % RC == 0, "internal: column chunk does not divide the padded column count");
   }
@@ -867,7 +867,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
   // Small one-column FP64 products: when splits of 256 sources leave CUs idle, the sources are split in
   // multiples of 64 (the direct kernel's 64-point tile form) for about two blocks per CU.
   if (prec == KRR_FP64 && !sym && !f64m && !block && R == 1 && DV == 0 && TM == 1 && split_req <= 0 &&
-      D <= 16 && per_split * split < device_cus()) {
+      (D <= 16 || D > 32) && per_split * split < device_cus()) {
     const int64_t sp = std::min<int64_t>(std::max<int64_t>(1, nsrc / 64), ceil_div(2 * device_cus(), per_split));
     src_len = round_up(ceil_div(nsrc, sp), 64);
     split = ceil_div(nsrc, src_len);

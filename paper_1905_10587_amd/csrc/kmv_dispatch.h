@@ -42,7 +42,7 @@ bool with_coordinates(int d, F f) {
 }
 
 // FP64 / FP32 direct kernels: D in {2,3,4,6,8,16,32,64,128}, TM in {1,2,4} (D >= 32: TM 1),
-// RC in {1,4,8}, DV in {0,2}; FP64 also RC in {16, 32} with TM 1, DV 0, D <= 16.  Return false if the
+// RC in {1,4,8}, DV in {0,2}; FP64 with D > 32 has 64 targets to a block; FP64 also RC in {16, 32} with TM 1, DV 0, D <= 16.  Return false if the
 // combination is not instantiated.
 bool launch_kmv_f64(int D, int TM, int RC, int DV, const KmvGrid& g, const double* xt, const double* xs,
                     const double* v, double neg_c, double* part, hipStream_t s);

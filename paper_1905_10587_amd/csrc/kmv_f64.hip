@@ -20,6 +20,18 @@ static void go64(const KmvGrid& g, const double* xt, const double* xs, const dou
   else go(std::integral_constant<int, D>{});
 }
 
+// More than 32 coordinates (64 targets to a block).
+template <int RC, int DV>
+static void go64w(const KmvGrid& g, int D, const double* xt, const double* xs, const double* v, double neg_c, double* part,
+                  hipStream_t s) {
+  if (g.occ) {
+    KRR_CHECK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(g.occ, k_kmv_f64_wide<RC, DV>, 256, 0));
+    return;
+  }
+  hipLaunchKernelGGL((k_kmv_f64_wide<RC, DV>), g.grid, dim3(256), 0, s, xt, xs, v, g.Rp, g.src_len, g.n_src, g.d, D,
+                     neg_c, part, g.mpad, g.Rout);
+}
+
 #define KRR_DV(D, TM, RC)                                   \
   if (DV == 0) { go64<D, TM, RC, 0>(g, xt, xs, v, neg_c, part, s); return true; } \
   if (DV == 2) { go64<D, TM, RC, 2>(g, xt, xs, v, neg_c, part, s); return true; }
@@ -112,6 +124,14 @@ bool launch_kmv_f64_sym(int D, int TM, const KmvGrid& g, const double* x, const 
 
 bool launch_kmv_f64(int D, int TM, int RC, int DV, const KmvGrid& g, const double* xt, const double* xs,
                     const double* v, double neg_c, double* part, hipStream_t s) {
+  if (D > 32) {
+    if (g.src_len % 64 != 0) return false;
+#define KRR_W64(R_, V_) \
+  if (RC == R_ && DV == V_) { go64w<R_, V_>(g, D, xt, xs, v, neg_c, part, s); return true; }
+    KRR_W64(1, 0) KRR_W64(1, 2) KRR_W64(4, 0) KRR_W64(4, 2) KRR_W64(8, 0) KRR_W64(8, 2)
+#undef KRR_W64
+    return false;
+  }
   if (g.src_len % 256 != 0) {   // short source splits: the 64-point tile form (one column, K only, D <= 16)
     if (TM != 1 || RC != 1 || DV != 0 || g.src_len % 64 != 0) return false;
     switch (D) {
@@ -132,8 +152,6 @@ bool launch_kmv_f64(int D, int TM, int RC, int DV, const KmvGrid& g, const doubl
     case 8: KRR_TM3(8) break;
     case 16: KRR_TM3(16) break;
     case 32: KRR_TM1(32) break;
-    case 64: KRR_TM1(64) break;
-    case 128: KRR_TM1(128) break;
   }
   return false;
 }

@@ -39,6 +39,101 @@ __device__ __forceinline__ double exp2_neg_f64(double q) {
 // exp(-t) for t >= 0
 __device__ __forceinline__ double exp_neg_f64(double t) { return exp2_neg_f64(-t * kLog2e); }
 
+// ------------------------------------------------------------------ direct FP64 kernel of many coordinates
+// Block: 64 targets x 64 sources at a time, a thread 4 x 4 of the pairs; the coordinates come through LDS sixteen at a
+// time.  With 33 to 128 coordinates a target does not fit a thread's registers (the form below spilled: 511 x 20 points,
+// d = 90 1.4 ms, now 8 us of a call of 50; 10000 x
+// 30000 points, d = 90 44 ms, now 2.4).  Bound by FP64 issue (2 d + 17 operations a pair) and, equally, by LDS reads (8 for 32
+// operations).  grid.y splits the sources, grid.z the column chunks.
+template <int RC, int DV>
+__global__ __launch_bounds__(256) void k_kmv_f64_wide(const double* __restrict__ xt, const double* __restrict__ xs,
+                                                      const double* __restrict__ v, int Rp, int64_t src_len,
+                                                      int64_t n_src, int d, int dpad, double neg_c,
+                                                      double* __restrict__ part, int64_t mpad, int Rout) {
+  constexpr int NO = DV == 2 ? 2 : 1;
+  constexpr int KC = 16, LD = 66;
+  __shared__ double sx[KC][LD], sy[KC][LD];
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  const int64_t i0 = (int64_t)blockIdx.x * 64;
+  const int c0 = blockIdx.z * RC;
+  const int64_t jb = (int64_t)blockIdx.y * src_len;
+  const int64_t je = jb + src_len < n_src ? jb + src_len : n_src;
+  const int row = tid >> 2, k4 = (tid & 3) * 4;
+  double acc[4][RC][NO];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int c = 0; c < RC; ++c)
+#pragma unroll
+      for (int o = 0; o < NO; ++o) acc[a][c][o] = 0.0;
+  for (int64_t j0 = jb; j0 < je; j0 += 64) {
+    double d2[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) d2[a][b] = 0.0;
+    for (int k0 = 0; k0 < d; k0 += KC) {   // (dpad is a multiple of 16)
+      double px[4], py[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        px[u] = xt[(i0 + row) * dpad + k0 + k4 + u];
+        py[u] = xs[(j0 + row) * dpad + k0 + k4 + u];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        sx[k4 + u][row] = px[u];
+        sy[k4 + u][row] = py[u];
+      }
+      __syncthreads();
+#pragma unroll 4
+      for (int k = 0; k < KC; ++k) {
+        double x[4], y[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) x[a] = sx[k][ty + 16 * a];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) y[b] = sy[k][tx + 16 * b];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const double df = x[a] - y[b];
+            d2[a][b] = __builtin_fma(df, df, d2[a][b]);
+          }
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      double vj[RC];
+#pragma unroll
+      for (int c = 0; c < RC; ++c) vj[c] = v[(j0 + tx + 16 * b) * Rp + c0 + c];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const double q = d2[a][b] * neg_c;
+        const double e = exp2_neg_f64(q);
+        const double ed = -kLn2 * q * e;   // (D^2/eps) K
+#pragma unroll
+        for (int c = 0; c < RC; ++c) {
+          acc[a][c][0] = __builtin_fma(e, vj[c], acc[a][c][0]);
+          if (DV == 2) acc[a][c][NO - 1] = __builtin_fma(ed, vj[c], acc[a][c][NO - 1]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    double* prow = part + ((int64_t)blockIdx.y * mpad + i0 + ty + 16 * a) * Rout;
+#pragma unroll
+    for (int c = 0; c < RC; ++c)
+#pragma unroll
+      for (int o = 0; o < NO; ++o) {
+        double s = acc[a][c][o];
+        for (int w = 8; w > 0; w >>= 1) s += __shfl_xor(s, w);
+        if (tx == 0) prow[(o ? Rp : 0) + c0 + c] = s;
+      }
+  }
+}
+
 // ------------------------------------------------------------------ direct kernels (FP64 / FP32)
 // Block: 256 threads, each owns TM targets (strided by 256) and RC columns.  Sources stream through
 // LDS in tiles of TS points (coalesced cooperative loads); every wave then reads a source's

@@ -102,3 +102,10 @@ def test_many_columns_without_a_block_kernel(gpu_lib, prec, n, d, R, deriv):
                                        (15, 7, 0), (17, 1, 0), (20, 3, 0), (21, 1, 2), (26, 6, 0), (27, 1, 0), (32, 7, 0)])
 def test_direct_counts(gpu_lib, prec, d, R, deriv):
     _check(gpu_lib, 2100, 4200, d, R, deriv, prec=prec)
+
+
+# FP64, 33 to 128 coordinates: sixteens of coordinates, one target to several tiles, column chunks, both kernels
+@pytest.mark.parametrize("m,n,d,R,deriv", [(1, 1, 33, 1, 0), (20, 511, 90, 1, 0), (65, 257, 48, 1, 2), (300, 1000, 64, 4, 0),
+                                           (64, 5000, 65, 9, 2), (1000, 70, 128, 3, 0), (257, 256, 49, 1, 1)])
+def test_many_coordinates(gpu_lib, m, n, d, R, deriv):
+    _check(gpu_lib, m, n, d, R, deriv)
