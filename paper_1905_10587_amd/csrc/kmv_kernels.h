@@ -41,10 +41,9 @@ __device__ __forceinline__ double exp_neg_f64(double t) { return exp2_neg_f64(-t
 
 // ------------------------------------------------------------------ direct FP64 kernel of many coordinates
 // Block: 64 targets x 64 sources at a time, a thread 4 x 4 of the pairs; the coordinates come through LDS sixteen at a
-// time.  With 33 to 128 coordinates a target does not fit a thread's registers (the form below spilled: 511 x 20 points,
-// d = 90 1.4 ms, now 8 us of a call of 50; 10000 x
-// 30000 points, d = 90 44 ms, now 2.4).  Bound by FP64 issue (2 d + 17 operations a pair) and, equally, by LDS reads (8 for 32
-// operations).  grid.y splits the sources, grid.z the column chunks.
+// time.  With 33 to 128 coordinates a target does not fit a thread's registers (the form below spilled: 20 x 511 points,
+// d = 90 1.59 ms a call, now 50 us; 10000 x 30000 44 ms, now 2.4).  Bound by FP64 issue (2 d + 17 operations a pair) and,
+// equally, by LDS reads (8 for 32 operations).  grid.y splits the sources, grid.z the column chunks.
 template <int RC, int DV>
 __global__ __launch_bounds__(256) void k_kmv_f64_wide(const double* __restrict__ xt, const double* __restrict__ xs,
                                                       const double* __restrict__ v, int Rp, int64_t src_len,
