@@ -7,6 +7,7 @@
 #include "scan.h"
 
 #include <algorithm>
+#include <mutex>
 
 namespace krr {
 
@@ -122,15 +123,38 @@ __global__ __launch_bounds__(256) void k_scan_final(ScanArgs a, const double* __
   }
 }
 
-// Pinned, device-visible result words (one set per thread, kept for the life of the process; a scan is waited for
-// before it returns, so a thread has one in flight).
-double* scan_words() {
-  thread_local double* w = nullptr;
-  if (!w) KRR_CHECK_HIP(hipHostMalloc((void**)&w, sizeof(double) * (kSegs + kPart), hipHostMallocDefault));
+// Pinned, device-visible result words: taken for a scan, given back when it has been waited for, so there are as many as
+// scans have ever been in flight at once.
+struct WordPool {
+  std::mutex mu;
+  std::vector<double*> free;
+};
+WordPool& word_pool() {
+  static WordPool* p = new WordPool;   // (never destroyed: a scan may end during exit)
+  return *p;
+}
+double* take_words() {
+  WordPool& p = word_pool();
+  {
+    std::lock_guard<std::mutex> l(p.mu);
+    if (!p.free.empty()) {
+      double* w = p.free.back();
+      p.free.pop_back();
+      return w;
+    }
+  }
+  double* w = nullptr;
+  KRR_CHECK_HIP(hipHostMalloc((void**)&w, sizeof(double) * (kSegs + kPart), hipHostMallocPortable));
   return w;
 }
 
 }  // namespace
+
+void ReturnWords::operator()(double* w) const {
+  WordPool& p = word_pool();
+  std::lock_guard<std::mutex> l(p.mu);
+  p.free.push_back(w);
+}
 
 ScanTicket scan_launch(const ScanInput* in, int count, int stats, PointScan* ps, int dpad, bool flags, hipStream_t s) {
   KRR_REQUIRE(count >= 1 && count <= kSegs && stats < count && dpad <= 256, "internal: bad scan");
@@ -138,12 +162,13 @@ ScanTicket scan_launch(const ScanInput* in, int count, int stats, PointScan* ps,
   tk.count = count;
   tk.stats = stats;
   tk.ps = ps;
-  tk.host = scan_words();
+  tk.host.reset(take_words());
+  double* host = tk.host.get();
   ScanArgs a{};
   a.nseg = count;
   a.stats = stats;
   int blocks = 0;
-  for (int i = 0; i < kSegs; ++i) tk.host[i] = 0.0;
+  for (int i = 0; i < kSegs; ++i) host[i] = 0.0;
   for (int i = 0; i < count; ++i) {
     tk.in[i] = in[i];
     Seg& g = a.seg[i];
@@ -159,20 +184,20 @@ ScanTicket scan_launch(const ScanInput* in, int count, int stats, PointScan* ps,
   DevBuf<double> part(stats >= 0 ? (size_t)a.seg[stats].blocks * kPart : 0, s);
   if (flags) tk.flags.alloc(blocks, s);
   if (stats >= 0 && dpad > 0) ps->center.alloc(dpad, s);
-  hipLaunchKernelGGL(k_scan, dim3((unsigned)blocks), dim3(256), 0, s, a, part.p, tk.host,
+  hipLaunchKernelGGL(k_scan, dim3((unsigned)blocks), dim3(256), 0, s, a, part.p, host,
                      tk.flags.p);
   if (stats >= 0)
-    hipLaunchKernelGGL(k_scan_final, dim3(1), dim3(256), 0, s, a, (const double*)part.p, ps->center.p, dpad, tk.host);
+    hipLaunchKernelGGL(k_scan_final, dim3(1), dim3(256), 0, s, a, (const double*)part.p, ps->center.p, dpad, host);
   KRR_LAUNCH_CHECK();
   return tk;
 }
 
 void scan_wait(const ScanTicket& t) {
   for (int i = 0; i < t.count; ++i)
-    if (t.host[i] != 0.0) throw Error{KRR_EINVAL, std::string(t.in[i].name) + " contains NaN or Inf"};
+    if (t.host.get()[i] != 0.0) throw Error{KRR_EINVAL, std::string(t.in[i].name) + " contains NaN or Inf"};
   if (t.stats < 0) return;
   const int d = t.in[t.stats].d;
-  const double* h = t.host + kSegs;
+  const double* h = t.host.get() + kSegs;
   t.ps->lo.assign(h, h + d);
   t.ps->hi.assign(h + KRR_MAX_D, h + KRR_MAX_D + d);
   t.ps->mean.assign(h + 2 * KRR_MAX_D, h + 2 * KRR_MAX_D + d);
