@@ -64,12 +64,13 @@ struct StageJob {
   float* o32 = nullptr;
   uint16_t* o16 = nullptr;
   int64_t total = 0;  // threads
-  int first = 0;      // block
+  int64_t first = 0;  // block
 };
 struct StageBatch {
   static constexpr int kJobs = 6;
   StageJob job[kJobs];
-  int count = 0, blocks = 0;
+  int count = 0;
+  int64_t blocks = 0;
   void add(StageJob j, int64_t threads);
   void launch(hipStream_t s);
 };

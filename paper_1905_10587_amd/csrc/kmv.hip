@@ -133,10 +133,11 @@ __device__ __forceinline__ void stage_vec(const StageJob& g, int64_t idx) {
 
 // The jobs one after another over the grid; a launch each (and its dependency) would cost a small call 4 us a job.
 __global__ __launch_bounds__(256) void k_stage(StageBatch b) {
+  const int64_t block = flat_block();
   int j = 0;
-  while (j + 1 < b.count && (int)blockIdx.x >= b.job[j + 1].first) ++j;
+  while (j + 1 < b.count && block >= b.job[j + 1].first) ++j;
   const StageJob& g = b.job[j];
-  const int64_t t = (int64_t)((int)blockIdx.x - g.first) * 256 + threadIdx.x;
+  const int64_t t = (block - g.first) * 256 + threadIdx.x;
   if (t >= g.total) return;
   if (g.kind == StageJob::kVector) stage_vec(g, t);
   else if (g.kind == StageJob::kSplitTarget || g.kind == StageJob::kSplitSource) stage_split(g, t);
@@ -147,13 +148,13 @@ void StageBatch::add(StageJob j, int64_t threads) {
   KRR_REQUIRE(count < kJobs, "internal: too many staging jobs");
   j.total = threads;
   j.first = blocks;
-  blocks += (int)ceil_div(threads, 256);
+  blocks += ceil_div(threads, 256);
   job[count++] = j;
 }
 
 void StageBatch::launch(hipStream_t s) {
   if (!count) return;
-  hipLaunchKernelGGL(k_stage, dim3((unsigned)blocks), dim3(256), 0, s, *this);
+  hipLaunchKernelGGL(k_stage, flat_grid(blocks), dim3(256), 0, s, *this);
   KRR_LAUNCH_CHECK();
   count = blocks = 0;
 }
@@ -370,7 +371,7 @@ __global__ __launch_bounds__(256) void k_kmv_finish_one(const double* __restrict
                                                         int64_t ldu, double* __restrict__ dot) {
   __shared__ double sum[3][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * kFinishRows + lane;
+  const int64_t block = flat_block(), i = block * kFinishRows + lane;
   double acc = 0.0;
   if (i < m) {
 #pragma unroll 8
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(256) void k_kmv_finish_one(const double* __restrict
   }
   if (DOT) {
     for (int o = 32; o > 0; o >>= 1) pq += __shfl_xor(pq, o);
-    if (lane == 0) dot[blockIdx.x] = pq;
+    if (lane == 0 && block * kFinishRows < m) dot[block] = pq;
   }
 }
 
@@ -929,7 +930,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
   const int has_shift = shift_host != nullptr;
   KRR_REQUIRE(!dot || (R == 1 && deriv == 0 && RoutK == 1 && !V.cols), "internal: p^T q is for one column");
   if (R == 1 && deriv == 0 && RoutK == 1 && !V.cols) {
-    const dim3 grid((unsigned)ceil_div(T.n, kFinishRows));
+    const dim3 grid = flat_grid(ceil_div(T.n, kFinishRows));
     const double sh = has_shift ? shift_host[0] : 0.0;
     if (dot)
       hipLaunchKernelGGL(k_kmv_finish_one<true>, grid, dim3(256), 0, s, (const double*)part.p, (int)split, T.npad, T.n,

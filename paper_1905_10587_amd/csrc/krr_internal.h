@@ -89,6 +89,16 @@ struct DevBuf {
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
+// ------------------------------------------------------------------ launches
+// A grid of `blocks` blocks (or a few more, in its last row) for kernels that number them by flat_block().  A launch
+// holds fewer than 2^32 threads along x, and one with more runs with their count cut off, without an error: 2^24 blocks
+// of 256 threads, which a billion rows reach.
+inline dim3 flat_grid(int64_t blocks) {
+  constexpr int64_t row = (int64_t)1 << 20;
+  return blocks <= row ? dim3((unsigned)blocks) : dim3((unsigned)row, (unsigned)ceil_div(blocks, row));
+}
+__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // ------------------------------------------------------------------ validation
 void check_finite_device(const double* p, int64_t count, const char* what, hipStream_t s);
 

@@ -126,7 +126,8 @@ __global__ __launch_bounds__(256) void k_wb_nz(const TW* __restrict__ W, int64_t
                                                const double* __restrict__ invb, double* out) {
   __shared__ double red[4][4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, m = lane & 15, k = lane >> 4;
-  const int64_t i0 = (int64_t)blockIdx.x * (16 * RT);
+  const int64_t i0 = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * (16 * RT);   // (rows over x and z: flat_grid)
+  if (i0 >= n) return;
   const int x0 = blockIdx.y * NT * kC;
   const TW* row[RT];
   f64x4 acc[RT][NT];
@@ -219,7 +220,8 @@ static void apply_tiles(const krr_precond& P, const TW* W, const std::vector<Dev
   const unsigned gy = (unsigned)ceil_div(rp, NT * kC);
   auto nz = [&](auto rt) {
     constexpr int RT = decltype(rt)::value;
-    hipLaunchKernelGGL((k_wb_nz<TW, NT, RT>), dim3((unsigned)ceil_div(n, 16 * RT), gy), dim3(256), 0, s, W, n, kept,
+    const dim3 rows = flat_grid(ceil_div(n, 16 * RT));
+    hipLaunchKernelGGL((k_wb_nz<TW, NT, RT>), dim3(rows.x, gy, rows.y), dim3(256), 0, s, W, n, kept,
                        (const double*)w.Z.p, rp, X, R, (const double*)w.invb.p, out);
   };
   // two row tiles to a block halve its reads of Z; where that still leaves two blocks to a compute unit
