@@ -3,7 +3,7 @@
 //   on the Cholesky factor (FP64 handles): K = L L^T and L R = U diag(sigma) with R orthogonal give
 //     K = U diag(sigma^2) U^T, so the eigenvectors are the rotated columns themselves, normalised, and the rotations
 //     are never accumulated (half the memory traffic); the factor is also much closer to orthogonal columns than K is
-//     (10 to 12 sweeps against 15 to 20 at k = 150 .. 1000);
+//     (random anchors, k = 150 .. 1600: 10 to 13 sweeps against 15 to 19);
 //   on K itself, K R = U diag(lambda) with R = U accumulated (handles with an FP32 copy of the factor).  The FP32
 //     rounding of W turns the last bits of the eigenvectors into differences of up to 1e-9 in an applied vector, so
 //     these handles keep this form, whose sums and products are taken in a fixed order that no launch choice changes.
@@ -45,7 +45,8 @@ struct Rotation {
 // The rotation that orthogonalises two columns of squared norms a, b and inner product g (none at a cosine of 1e-15
 // or below).  IEEE: t, c and s by correctly rounded operations (the form on K, see above); otherwise the same root
 // without the division by g and with the short reciprocals (a rotation step is a serial chain of these: k = 150,
-// 13.9 -> 8.4 us a round).
+// 13.9 -> 8.4 us a round), c then corrected.  |W W^T - K| over anchors alone, 1000 points, d = 4: 1.6e-14 (c as the
+// reciprocal root leaves it: 2.8e-13; IEEE operations, which round 1 + t^2, its root and the quotient: 3.0e-13).
 constexpr double kTol2 = 1e-30;
 template <bool IEEE>
 __device__ __forceinline__ Rotation rotation(double a, double b, double g) {
@@ -59,7 +60,11 @@ __device__ __forceinline__ Rotation rotation(double a, double b, double g) {
       const double d = b - a, h = 2.0 * g;
       const double q = __builtin_fma(d, d, h * h);
       r.t = copysign(1.0, d) * h * rcp_nr(__builtin_fma(q, rsqrt_nr(q), fabs(d)));
-      r.c = rsqrt_nr(__builtin_fma(r.t, r.t, 1.0));
+      // c to half a unit: a Newton step on the error of its square against 1 + t^2 = w + dw.  t's own rounding leaves a
+      // rotation a rotation, but a c one unit off scales both columns, and a column goes through thousands of steps.
+      const double w = __builtin_fma(r.t, r.t, 1.0), dw = __builtin_fma(r.t, r.t, 1.0 - w);
+      const double c = rsqrt_nr(w), c2 = c * c, e = __builtin_fma(c, c, -c2);
+      r.c = __builtin_fma(0.5 * c, __builtin_fma(-c2, dw, __builtin_fma(-c2, w, 1.0)) - e * w, c);
     }
     r.s = r.c * r.t;
   }
@@ -383,7 +388,8 @@ int jacobi_evd(const double* K, double* V, double* lam, int k, bool on_factor, h
   if (on_factor) {
     // A numerically singular block (its smallest eigenvalues are rounding noise) is factored with a shift of a few
     // roundings of its largest possible row sum, taken off the eigenvalues again; the shift grows until the
-    // factorisation succeeds (its own error is below k^2 u, reached after two steps at most).
+    // factorisation succeeds.  K's roundings and its own are below k^2 u, which the fourth shift exceeds up to k = 60000
+    // (the refusal after eight is for a block that is no kernel matrix).
     DevBuf<double> C((size_t)k * k, s), L((size_t)k * k, s);
     for (int attempt = 0;; ++attempt) {
       hipLaunchKernelGGL(k_shifted, dim3(nk), dim3(256), 0, s, K, k, shift, C.p);
@@ -410,9 +416,10 @@ int jacobi_evd(const double* K, double* V, double* lam, int k, bool on_factor, h
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   }
   DevBuf<unsigned long long> off(1, s);
-  // A sweep's measure is the largest cosine it met before its rotations, and by then convergence is quadratic, with a
-  // constant of at most the inverse of the smallest relative gap: 1e-10 leaves less than 1e-13 down to gaps of 1e-7.
-  const double stop = on_factor ? 1e-10 : 1e-13;
+  // A sweep's measure is the largest cosine that it met before its rotations.  The last sweep has to start at 1e-13: the
+  // quadratic convergence that would allow more needs relative gaps that a block near the identity (points far apart:
+  // cosines of 1e-11 and gaps no larger) does not have.
+  constexpr double kStop = 1e-13;
   double *cur = A.p, *next = A2.p;
   int sweep = 0;
   for (; sweep < max_sweeps; ++sweep) {
@@ -434,7 +441,7 @@ int jacobi_evd(const double* K, double* V, double* lam, int k, bool on_factor, h
     KRR_CHECK_HIP(hipStreamSynchronize(s));
     double offv;
     std::memcpy(&offv, &h, sizeof(offv));
-    if (offv <= stop) { ++sweep; break; }
+    if (offv <= kStop) { ++sweep; break; }
   }
   hipLaunchKernelGGL(k_columns_to_evd, dim3((unsigned)k), dim3(256), 0, s, (const double*)cur, (const double*)R.p, k, kp,
                      shift, V, lam);
