@@ -336,7 +336,10 @@ int krr_num_variants(int32_t prec, int32_t R);
  * variant, else the default; n <= 0: sizes unknown) and whether it is the symmetric form (square product
  * K(X, X) V of one column without the derivative kernel, mixed or FP64: each off-diagonal pair of point tiles
  * is evaluated once).  square != 0: targets and sources are the same point set.  variant, symmetric [host]
- * out.  Host only; no GPU call.  KRR_EINVAL on bad arguments.
+ * out.  -1 and 0 for a square FP64 product of n > 0 points that runs no variant: few pairs are formed straight from the
+ * caller's arrays (krr_kernel_mv: m n up to 2^23 with one column and d <= 8, 2^20 with d <= 16, half of that with 2 .. 8
+ * columns; K' with one column only).  A cross-set product of few pairs runs none either, but its m is not asked for here.
+ * Host only; no GPU call.  KRR_EINVAL on bad arguments.
  */
 int krr_kmv_variant(int32_t d, int32_t R, int32_t deriv, int32_t prec, int32_t square, int64_t n, int32_t* variant,
                     int32_t* symmetric);
@@ -353,14 +356,14 @@ int krr_kmv_variant(int32_t d, int32_t R, int32_t deriv, int32_t prec, int32_t s
  * launched.
  */
 int krr_set_cull(int32_t mode);
-/* Pairs of the last kernel MVM launched on this thread: pairs_total = npad^2 (npad the point count padded to
+/* Pairs of the last kernel MVM launched on this thread: pairs_total = npad^2 (npad the target count padded to
  * a multiple of 1024), pairs_skipped = those whose evaluation culling skipped (0 if it did not run).
  * Synchronises the stream.  [host] outputs. */
 int krr_cull_stats(int64_t* pairs_total, int64_t* pairs_skipped, void* stream);
 
 /* What the last kernel MVM launched on this thread ran: its variant, its split (sources per block of a direct
  * form, super-tile edge of a symmetric form) and whether it was the symmetric form.  -1 / 0 / 0 before any
- * launch.  Host only. */
+ * launch; variant -1 with the sources per block for a product of few FP64 pairs (krr_kmv_variant).  Host only. */
 int krr_kmv_last_launch(int32_t* variant, int32_t* split, int32_t* symmetric);
 
 #ifdef __cplusplus

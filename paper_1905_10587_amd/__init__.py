@@ -535,7 +535,7 @@ def num_variants(prec, R: int = 1) -> int:
 
 def kmv_variant(d: int, R: int = 1, prec="mixed", *, deriv: int = 0, square: bool = True, n: int = 0):
     """(variant, symmetric): the kernel variant a product of n sources would run (n = 0: size unknown) and
-    whether it is the symmetric form."""
+    whether it is the symmetric form.  (-1, False): a square FP64 product of so few pairs that it runs none."""
     lib = load()
     v, sym = ctypes.c_int32(), ctypes.c_int32()
     _chk(lib, lib.krr_kmv_variant(d, R, deriv, _prec(prec), 1 if square else 0, int(n), ctypes.byref(v),
@@ -544,7 +544,8 @@ def kmv_variant(d: int, R: int = 1, prec="mixed", *, deriv: int = 0, square: boo
 
 
 def kmv_last_launch():
-    """(variant, split, symmetric) of the last kernel MVM launched on this thread."""
+    """(variant, split, symmetric) of the last kernel MVM launched on this thread; variant -1 with a split for a
+    product of few FP64 pairs, which runs none of the launch table's variants."""
     lib = load()
     v, sp, sym = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
     _chk(lib, lib.krr_kmv_last_launch(ctypes.byref(v), ctypes.byref(sp), ctypes.byref(sym)))

@@ -13,12 +13,11 @@ void validate_prec(int32_t prec) {
   KRR_REQUIRE(prec == KRR_FP64 || prec == KRR_FP32 || prec == KRR_MIXED, "unknown precision");
 }
 
-// Few FP64 pairs go straight from the caller's arrays (but a forced or tuned variant is taken as it is).  Not where the
-// result overlaps an input: staging copies first, and so allows that.
+// Few FP64 pairs go straight from the caller's arrays.  Not where the result overlaps an input: staging copies first, and
+// so allows that.
 static bool kmv_takes_small(const double* Xt, int64_t m, const double* Xs, int64_t n, int d, const double* V, int R,
                             int deriv, int prec, const double* U, int64_t ldu) {
-  if (!kmv_small_fits(m, n, d, R, deriv, prec)) return false;
-  if (kmv_lookup(prec, d, R, n, Xt == Xs && m == n && deriv == 0).variant >= 0) return false;
+  if (!kmv_prefers_small(m, n, d, R, deriv, prec, Xt == Xs && m == n)) return false;
   const double* end = U + (m - 1) * ldu + (deriv == 2 ? 2 : 1) * R;
   auto apart = [&](const double* p, int64_t count) { return end <= p || p + count <= U; };
   return apart(Xt, m * d) && apart(Xs, n * d) && apart(V, n * R);

@@ -138,6 +138,8 @@ struct ColumnShift {
   int on;
 };
 bool kmv_small_fits(int64_t m, int64_t n, int d, int R, int deriv, int prec);
+// Whether such a product is taken that way (where its result overlaps no input): a forced or tuned variant is taken as it is.
+bool kmv_prefers_small(int64_t m, int64_t n, int d, int R, int deriv, int prec, bool square);
 void kmv_small(const double* Xt, int64_t m, const double* Xs, int64_t n, int d, double eps, const double* V, int R,
                const double* shift, int deriv, double* U, int64_t ldu, const int* bad, int nbad, hipStream_t s);
 
@@ -161,12 +163,13 @@ struct KmvChoice {
   int split = 0;      // sources per block (direct forms) or super-tile edge (symmetric forms); 0: launcher's choice
 };
 struct KmvLaunchInfo {
-  int variant = -1, split = 0, symmetric = 0;
+  int variant = -1, split = 0, symmetric = 0;   // variant -1 with a split: a product straight from the arrays (kmv_small)
   int culled = 0;          // the symmetric form ran with far-tile culling (counters valid)
-  int64_t npad = 0;        // padded point count of the launch
+  int64_t npad = 0;        // target count padded to a multiple of kRowPad (whatever its staged copy holds)
   int nf = 0;              // target fragments per wave (16 NF targets per wave)
 };
 KmvLaunchInfo kmv_last_launch();
+void kmv_record_launch(const KmvLaunchInfo& info);
 KmvChoice kmv_lookup(int prec, int d, int R, int64_t n, bool square);
 void kmv_set_tuned(int prec, int d, int R, int64_t n, bool square, KmvChoice c);
 std::string device_arch();

@@ -449,6 +449,7 @@ std::string device_arch() {
 }
 
 KmvLaunchInfo kmv_last_launch() { return t_last; }
+void kmv_record_launch(const KmvLaunchInfo& info) { t_last = info; }
 
 // The shared-tile block forms (variants 12, 13) cover 128 columns per block in 32-column waves; with fewer
 // than 7/8 of those waves holding columns the idle ones cost more than the shared exp/split saves.
@@ -920,7 +921,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
   g.d = T.d;
   const size_t need = (size_t)split * T.npad * RoutK;
   if (part.n < need) part.alloc(need, s);
-  t_last = KmvLaunchInfo{variant, (int)(sym ? g.E : src_len), sym ? 1 : 0, cmask ? 1 : 0, T.npad, NF};
+  t_last = KmvLaunchInfo{variant, (int)(sym ? g.E : src_len), sym ? 1 : 0, cmask ? 1 : 0, round_up(T.n, kRowPad), NF};
   if (cmask) cull_reset_counters(s);
   if (kev) KRR_CHECK_HIP(hipEventRecord(kev[0], s));
   const bool ok = run(g);

@@ -145,6 +145,7 @@ void go_small(const SmallArgs& a) {
   if (per * TG > 64) S = std::max<int64_t>(1, std::min(ceil_div(1024, gx), per / 8));
   const int64_t len = ceil_div(a.n, S);
   S = ceil_div(a.n, len);
+  kmv_record_launch(KmvLaunchInfo{-1, (int)len, 0, 0, round_up(a.m, kRowPad), 0});
   const int cols = a.R * (DV == 2 ? 2 : 1);
   DevBuf<double> part(S > 1 ? (size_t)(S * a.m * cols) : 0, a.s);
   hipLaunchKernelGGL((k_kmv_small<D, TG, RC, DV>), dim3((unsigned)gx, (unsigned)S), dim3(256), 0, a.s, a.Xt, a.m, a.Xs, a.n,
@@ -180,6 +181,10 @@ bool kmv_small_fits(int64_t m, int64_t n, int d, int R, int deriv, int prec) {
   // 4000, d = 3).  Wide points and more columns leave fewer targets to a thread: at 2890 x 2890, d = 16 it is 163 us.
   const int64_t most = ((int64_t)1 << 23) >> ((d > 8 ? 3 : 0) + (R > 1 ? 1 : 0));
   return prec == KRR_FP64 && d <= 16 && (R == 1 || (R <= 8 && deriv == 0)) && m <= most / n;
+}
+
+bool kmv_prefers_small(int64_t m, int64_t n, int d, int R, int deriv, int prec, bool square) {
+  return kmv_small_fits(m, n, d, R, deriv, prec) && kmv_lookup(prec, d, R, n, square && deriv == 0).variant < 0;
 }
 
 void kmv_small(const double* Xt, int64_t m, const double* Xs, int64_t n, int d, double eps, const double* V, int R,
