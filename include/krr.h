@@ -319,8 +319,9 @@ int krr_grad(const double* Xtr, int64_t n, const double* ytr,
  * forms; the super-tile edge for the symmetric forms).  krr_autotune times every variant for (d, R, prec) on n synthetic points of a
  * square product, then the two fastest with the split halved and doubled, and records the fastest for the
  * size class floor(log2 n) in the process-wide table (key: precision, d, shape class of R, size class,
- * square or cross-set).  Every later product of that class launches the recorded entry; an entry forced with
- * krr_set_variant applies at every size.  best_variant [host] out.
+ * square or cross-set).  Every later product of that class launches the recorded entry, except FP64 products of
+ * few pairs, which run no variant (krr_kmv_variant); an entry forced with krr_set_variant applies at every size,
+ * to those too.  best_variant [host] out.
  * krr_autotune_save / krr_autotune_load persist the table as JSON with the GPU architecture it was tuned on;
  * loading a table tuned on another architecture returns KRR_EINVAL.
  */

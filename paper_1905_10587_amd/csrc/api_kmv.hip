@@ -17,7 +17,7 @@ void validate_prec(int32_t prec) {
 // so allows that.
 static bool kmv_takes_small(const double* Xt, int64_t m, const double* Xs, int64_t n, int d, const double* V, int R,
                             int deriv, int prec, const double* U, int64_t ldu) {
-  if (!kmv_prefers_small(m, n, d, R, deriv, prec, Xt == Xs && m == n)) return false;
+  if (!kmv_prefers_small(m, n, d, R, deriv, prec)) return false;
   const double* end = U + (m - 1) * ldu + (deriv == 2 ? 2 : 1) * R;
   auto apart = [&](const double* p, int64_t count) { return end <= p || p + count <= U; };
   return apart(Xt, m * d) && apart(Xs, n * d) && apart(V, n * R);

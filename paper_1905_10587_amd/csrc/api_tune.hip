@@ -46,7 +46,7 @@ extern "C" int krr_kmv_variant(int32_t d, int32_t R, int32_t deriv, int32_t prec
     KRR_REQUIRE(variant && symmetric, "null output pointer");
     *variant = -1;
     *symmetric = 0;
-    if (square && n > 0 && krr::kmv_prefers_small(n, n, d, R, deriv, prec, true)) return (int)KRR_OK;
+    if (square && n > 0 && krr::kmv_prefers_small(n, n, d, R, deriv, prec)) return (int)KRR_OK;
     const bool sq = square != 0 && deriv == 0;
     int v = krr::kmv_lookup(prec, d, R, n, sq).variant;
     if (v < 0) v = krr::kmv_default_variant(prec, d, R, n > 0 ? n : 0, n > 0 ? n : 0, sq);

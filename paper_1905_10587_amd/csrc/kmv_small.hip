@@ -183,8 +183,8 @@ bool kmv_small_fits(int64_t m, int64_t n, int d, int R, int deriv, int prec) {
   return prec == KRR_FP64 && d <= 16 && (R == 1 || (R <= 8 && deriv == 0)) && m <= most / n;
 }
 
-bool kmv_prefers_small(int64_t m, int64_t n, int d, int R, int deriv, int prec, bool square) {
-  return kmv_small_fits(m, n, d, R, deriv, prec) && kmv_lookup(prec, d, R, n, square && deriv == 0).variant < 0;
+bool kmv_prefers_small(int64_t m, int64_t n, int d, int R, int deriv, int prec) {
+  return kmv_small_fits(m, n, d, R, deriv, prec) && kmv_get_override(d, R, prec) < 0;
 }
 
 void kmv_small(const double* Xt, int64_t m, const double* Xs, int64_t n, int d, double eps, const double* V, int R,
