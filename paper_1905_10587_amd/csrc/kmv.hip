@@ -639,7 +639,10 @@ static int64_t device_cus() {
 }
 
 // Resident blocks of a kernel configuration on the current device (blocks per CU x CUs), cached by key.
-using LaunchKey = std::array<int, 6>;   // device, precision, d, shape class, variant and tile rows, derivative form
+// The key names the kernel: device, precision, d, shape class, variant and tile rows, derivative form, columns of a block.
+// (Without the columns the first count of a class fixed the blocks of all others, so that a product's split, and in
+// FP64 its last bits, depended on the calls before it: 128 columns after 16 ran with the 16-column kernel's count.)
+using LaunchKey = std::array<int, 7>;
 template <typename Query>
 static int64_t resident_blocks(Query query, LaunchKey k) {
   int dev = 0;
@@ -841,12 +844,14 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
   // The block path caps its FP64 partial buffer near 2 GB.
   KmvGrid q{dim3(1, 1, 1), 0, nsrc, T.npad, RpK, RoutK};
   q.d = T.d;
+  const int vtiles = V.Rb / 16;   // (launch_kmv_block_vt: eight column tiles to a block, or one block of fewer, or any)
+  const int key_cols = vtile ? (vtiles % 8 == 0 ? 8 : vtiles < 8 ? vtiles : 0) : block ? NRC : f64m ? NRG : RC;
   const int64_t cap = resident_blocks(
       [&](int* occ) {
         q.occ = occ;
         KRR_REQUIRE(run(q), "kernel variant not instantiated for this shape");
       },
-      LaunchKey{0, prec, T.d, rclass(prec, R), variant * 4096 + (int)rows, DV});
+      LaunchKey{0, prec, T.d, rclass(prec, R), variant * 4096 + (int)rows, DV, key_cols});
   int64_t smax = std::max<int64_t>(1, nsrc / 256);
   if (block) smax = std::min<int64_t>(smax, std::max<int64_t>(1, ((int64_t)1 << 28) / (T.npad * (int64_t)RoutK)));
   const int64_t per_split = gx * gz;
