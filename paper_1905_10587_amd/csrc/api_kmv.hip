@@ -75,13 +75,8 @@ extern "C" int krr_kernel_mv(const double* Xt, int64_t m, const double* Xs, int6
     const int count = same ? 2 : 3;
     if (krr::kmv_takes_small(Xt, m, Xs, n, d, V, R, deriv, prec, U, ldu)) {
       // needs only the flags of the scan, on the device: one synchronisation, after the product
-      const krr::ScanTicket t = krr::scan_launch(in, count, -1, nullptr, 0, true, s);
-      try {
-        krr::kmv_small(Xt, m, Xs, n, d, eps, V, R, shift, deriv, U, ldu, t.flags.p, (int)t.flags.n, s);
-      } catch (...) {
-        (void)hipStreamSynchronize(s);   // the scan still writes to its host words
-        throw;
-      }
+      krr::ScanTicket t = krr::scan_launch(in, count, -1, nullptr, 0, true, s);
+      krr::kmv_small(Xt, m, Xs, n, d, eps, V, R, shift, deriv, U, ldu, t.flags.p, (int)t.flags.n, s);
       KRR_CHECK_HIP(hipStreamSynchronize(s));
       krr::scan_wait(t);
     } else {

@@ -16,6 +16,7 @@ namespace {
 constexpr int kMaxBlocks = 512;   // per input
 constexpr int kSegs = 4;
 constexpr int kPart = 3 * KRR_MAX_D;
+static_assert(HostWords::kCount >= kSegs + kPart, "the scan's results");
 
 struct Seg {
   const double* p;
@@ -123,8 +124,6 @@ __global__ __launch_bounds__(256) void k_scan_final(ScanArgs a, const double* __
   }
 }
 
-// Pinned, device-visible result words: taken for a scan, given back when it has been waited for, so there are as many as
-// scans have ever been in flight at once.
 struct WordPool {
   std::mutex mu;
   std::vector<double*> free;
@@ -133,27 +132,32 @@ WordPool& word_pool() {
   static WordPool* p = new WordPool;   // (never destroyed: a scan may end during exit)
   return *p;
 }
-double* take_words() {
+
+}  // namespace
+
+HostWords::HostWords(hipStream_t s) : s_(s) {
   WordPool& p = word_pool();
   {
     std::lock_guard<std::mutex> l(p.mu);
     if (!p.free.empty()) {
-      double* w = p.free.back();
+      w_ = p.free.back();
       p.free.pop_back();
-      return w;
+      return;
     }
   }
-  double* w = nullptr;
-  KRR_CHECK_HIP(hipHostMalloc((void**)&w, sizeof(double) * (kSegs + kPart), hipHostMallocPortable));
-  return w;
+  KRR_CHECK_HIP(hipHostMalloc((void**)&w_, sizeof(double) * kCount, hipHostMallocPortable));
 }
 
-}  // namespace
-
-void ReturnWords::operator()(double* w) const {
-  WordPool& p = word_pool();
-  std::lock_guard<std::mutex> l(p.mu);
-  p.free.push_back(w);
+HostWords::~HostWords() {
+  if (!w_) return;
+  if (busy_) (void)hipStreamSynchronize(s_);
+  try {
+    WordPool& p = word_pool();
+    std::lock_guard<std::mutex> l(p.mu);
+    p.free.push_back(w_);
+  } catch (...) {   // (no memory for the list)
+    (void)hipHostFree(w_);
+  }
 }
 
 ScanTicket scan_launch(const ScanInput* in, int count, int stats, PointScan* ps, int dpad, bool flags, hipStream_t s) {
@@ -162,7 +166,7 @@ ScanTicket scan_launch(const ScanInput* in, int count, int stats, PointScan* ps,
   tk.count = count;
   tk.stats = stats;
   tk.ps = ps;
-  tk.host.reset(take_words());
+  tk.host = HostWords(s);
   double* host = tk.host.get();
   ScanArgs a{};
   a.nseg = count;
@@ -184,6 +188,7 @@ ScanTicket scan_launch(const ScanInput* in, int count, int stats, PointScan* ps,
   DevBuf<double> part(stats >= 0 ? (size_t)a.seg[stats].blocks * kPart : 0, s);
   if (flags) tk.flags.alloc(blocks, s);
   if (stats >= 0 && dpad > 0) ps->center.alloc(dpad, s);
+  tk.host.busy();
   hipLaunchKernelGGL(k_scan, dim3((unsigned)blocks), dim3(256), 0, s, a, part.p, host,
                      tk.flags.p);
   if (stats >= 0)
@@ -192,7 +197,8 @@ ScanTicket scan_launch(const ScanInput* in, int count, int stats, PointScan* ps,
   return tk;
 }
 
-void scan_wait(const ScanTicket& t) {
+void scan_wait(ScanTicket& t) {
+  t.host.done();
   for (int i = 0; i < t.count; ++i)
     if (t.host.get()[i] != 0.0) throw Error{KRR_EINVAL, std::string(t.in[i].name) + " contains NaN or Inf"};
   if (t.stats < 0) return;
@@ -204,7 +210,7 @@ void scan_wait(const ScanTicket& t) {
 }
 
 void scan_inputs(const ScanInput* in, int count, int stats, PointScan* ps, int dpad, hipStream_t s) {
-  const ScanTicket t = scan_launch(in, count, stats, ps, dpad, false, s);
+  ScanTicket t = scan_launch(in, count, stats, ps, dpad, false, s);
   KRR_CHECK_HIP(hipStreamSynchronize(s));
   scan_wait(t);
 }

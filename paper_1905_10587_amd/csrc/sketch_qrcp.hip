@@ -18,6 +18,7 @@
 #include "gemm.h"
 #include "kmv_kernels.h"
 #include "radix_sort.h"
+#include "scan.h"
 #include "sketch_qrcp.h"
 
 namespace krr {
@@ -961,13 +962,6 @@ static void refresh_pass(const T* Yt, int64_t ldy, int64_t N, int l, const doubl
   KRR_LAUNCH_CHECK();
 }
 
-// Pinned, device-visible word for the steps of a batch (one per thread, kept for the life of the process).
-static int* steps_word() {
-  thread_local int* w = nullptr;
-  if (!w) KRR_CHECK_HIP(hipHostMalloc((void**)&w, sizeof(int), hipHostMallocDefault));
-  return w;
-}
-
 struct QrEvent {
   hipEvent_t e = nullptr;
   QrEvent() { KRR_CHECK_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming)); }
@@ -992,7 +986,8 @@ static void qrcp_cand(const T* Yt, int64_t ldy, int64_t N, int l, int k, int64_t
   DevBuf<unsigned> hist(kQrBins, s);
   DevBuf<QrState> state(1, s);
   QrState* st = state.p;
-  int* steps_host = steps_word();
+  HostWords words(s);
+  int* steps_host = reinterpret_cast<int*>(words.get());
   QrEvent ev;
   KRR_CHECK_HIP(hipMemsetAsync(hist.p, 0, hist.bytes(), s));
   KRR_CHECK_HIP(hipMemsetAsync(st, 0, sizeof(QrState), s));
@@ -1049,6 +1044,7 @@ static void qrcp_cand(const T* Yt, int64_t ldy, int64_t N, int l, int k, int64_t
         Rp = R.p;
       }
       gram_tile(Rp, kQrCand, l, kQrCand, G.p, kQrCand, s);
+      words.busy();
       hipLaunchKernelGGL(k_qr_pivots, dim3(1), dim3(kQrCand / 2), 0, s, (const double*)G.p, st, (const int*)cidx.p, j0, nb,
                          nrm2.p, piv, rdiag, Lpp.p, psel.p, steps_host);
       KRR_CHECK_HIP(hipEventRecord(ev.e, s));
@@ -1068,6 +1064,7 @@ static void qrcp_cand(const T* Yt, int64_t ldy, int64_t N, int l, int k, int64_t
       KRR_LAUNCH_CHECK();
       // the host waits for the pivots only, and enqueues the next refresh while the directions are formed
       KRR_CHECK_HIP(hipEventSynchronize(ev.e));
+      words.done();
       steps = *steps_host;
     }
     KRR_REQUIRE(steps > 0, "pivoted QR: no valid pivot on fresh candidates");
