@@ -51,6 +51,7 @@ void woodbury_apply(const krr_precond& P, const double* x, WoodburyWork& w, bool
 constexpr int kBlockColumns = 256;
 void woodbury_block_prepare(const krr_precond& P, WoodburyWork& w, hipStream_t s);
 void woodbury_block_apply(const krr_precond& P, const double* X, WoodburyWork& w, bool use32, double* out, hipStream_t s);
+void woodbury_block_load(hipStream_t s);   // a tiny call of its products, which loads their code object (krr_init)
 
 // Its parts: rows per block of the pass W^T x, and z = G t.
 int woodbury_rows(int64_t n);

@@ -461,6 +461,9 @@ extern "C" int krr_init(void* stream) {
     krr::syrk_tn<float>(af.p, 8, 8, 8, c.p, 8, s);
     krr::gemm_tn<float, double>(af.p, 8, a.p, 8, 8, 8, 8, c.p, 8, s);
     krr::gemm_nn<double>(a.p, 8, a.p, 8, 8, 8, 8, c.p, 8, nullptr, 0, nullptr, s);
+    krr::gemm_tile(a.p, 8, a.p, 8, 8, 8, 8, c.p, 8, nullptr, 0, s);
+    krr::gram_tile(a.p, 8, 8, 8, c.p, 8, s);
+    krr::woodbury_block_load(s);
     KRR_CHECK_HIP(hipStreamSynchronize(s));
     (void)krr::noalloc_scratch();   // this device's address of the no-allocation entry point's scratch
     return (int)KRR_OK;

@@ -243,4 +243,24 @@ void woodbury_block_apply(const krr_precond& P, const double* X, WoodburyWork& w
   }
 }
 
+template <typename TW>
+static void touch(hipStream_t s) {
+  constexpr int n = 8, kp = 64, rp = kC, R = 2;
+  DevBuf<TW> W(n * n, s);
+  DevBuf<double> X(n * R, s), Z((size_t)kp * rp, s), out(n * R, s);
+  WoodburyWork w;
+  w.partial.alloc((size_t)kp * rp, s);
+  for (auto [p, bytes] : {std::pair<void*, size_t>{W.p, W.bytes()}, {X.p, X.bytes()}, {Z.p, Z.bytes()}})
+    KRR_CHECK_HIP(hipMemsetAsync(p, 0, bytes, s));
+  product_t<TW, 1>(W.p, n, n, X.p, R, R, rp, nullptr, R, 0, w, Z.p, s);
+  hipLaunchKernelGGL((k_wb_nz<TW, 1, 1>), dim3(1, 1), dim3(256), 0, s, (const TW*)W.p, (int64_t)n, n, (const double*)Z.p,
+                     rp, (const double*)X.p, R, (const double*)X.p, out.p);
+  KRR_LAUNCH_CHECK();
+}
+
+void woodbury_block_load(hipStream_t s) {
+  touch<double>(s);
+  touch<float>(s);
+}
+
 }  // namespace krr
