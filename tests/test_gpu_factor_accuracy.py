@@ -40,3 +40,15 @@ def test_rotations_keep_norms(gpu_lib, k, d, eps):
     assert abs(lam.sum() - k) <= walk * k
     # entries of W W^T: sums of k products with a walk each, and the kernel's own roundings (32 of them)
     np.testing.assert_allclose(W @ W.T, ok.kernel_matrix(X, X, eps), rtol=0, atol=2 * walk + (np.sqrt(k) + 32) * 2.0 ** -53)
+
+
+def test_rotations_by_single_rows(gpu_lib):
+    """More than 4800 anchors, mixed: the accumulated rotations are applied to one row at a time (four no longer fit in LDS)."""
+    k = 4810
+    X = np.random.default_rng(0).random((k, 8))
+    lam, W = _handle(gpu_lib, X, 0.05, "mixed")
+    rows = np.random.default_rng(1).choice(k, 300, replace=False)
+    K = ok.kernel_matrix(X[rows], X, 0.05)
+    # as above, with the operations of this form each rounded: 20 sweeps, three roundings a step and no mean of zero
+    assert abs(lam.sum() - k) <= 20 * k * 2.0 ** -53 * k
+    np.testing.assert_allclose(W[rows] @ W.T, K, rtol=0, atol=20 * k * 2.0 ** -53)
