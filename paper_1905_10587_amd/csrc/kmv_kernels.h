@@ -140,7 +140,8 @@ __global__ __launch_bounds__(256) void k_kmv_f64_wide(const double* __restrict__
 // grid.z the column chunks.
 template <int D>
 struct DirectTile {
-  static constexpr int TS = D <= 16 ? 256 : (D <= 32 ? 128 : 64);
+  static_assert(D <= 32, "wider points: k_kmv_f64_wide");
+  static constexpr int TS = D <= 16 ? 256 : 128;
 };
 
 // DR: coordinates evaluated (of D staged; the others are zeros and add nothing).
