@@ -243,9 +243,13 @@ typedef struct {
   int32_t n_mvm_fp64;     /* FP64 MVMs for residual replacement / final check */
   int32_t n_replace;      /* residual replacements performed */
   double t_total_ms;      /* wall time of the solve (host clock, stream synchronised) */
-  double t_mvm_ms;        /* HIP-event time in working-precision MVMs (if timing enabled) */
+  double t_mvm_ms;        /* HIP-event time in working-precision MVMs (if timing enabled); without their operand's
+                             staging where t_precond_ms holds it */
   double t_mvm_fp64_ms;   /* HIP-event time in FP64 MVMs */
-  double t_precond_ms;    /* HIP-event time in Woodbury applies */
+  double t_precond_ms;    /* HIP-event time in Woodbury applies.  One column with a preconditioner and at most 32768
+                             rows: the apply shares its passes with the rest of an iteration's vector work, and the
+                             time is that of both (the updates of x, r and the direction with their dot products and
+                             the direction's staging; not of a step that a replacement or check follows) */
   double kappa_est;       /* Lanczos estimate of the preconditioned condition number, column 0 */
   double t_mvm_kernel_ms; /* HIP-event time of the main MVM kernel alone (t_mvm_ms without operand
                              staging and the FP64 finishing pass) */

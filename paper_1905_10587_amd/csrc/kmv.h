@@ -40,7 +40,7 @@ struct Staged {
 };
 
 constexpr int kDotRows = 64;
-constexpr int kRowPad = 1024;   // targets/sources are padded to multiples of this
+constexpr int kRowPad = 1024;   // sources, and more than 8192 targets, are padded to multiples of this (staged_rows)
 constexpr int kPrefetchRows = 32;   // extra allocated rows after the padded sources (prefetch reads)
 
 // Pads d up to the instantiated widths of the direct (FP64/FP32) kernels.
@@ -75,8 +75,9 @@ struct StageBatch {
   void launch(hipStream_t s);
 };
 
-// Stage a point set (into batch, for its launch, where given).  ps: the scan of the operator's points; its centre is the translation of the staged copies (the
-// kernel is translation invariant; pass the same scan for targets and sources), nullptr: none (FP64 only).
+// Stage a point set (into batch, for its launch, where given).  ps: the scan of the operator's points; its centre is the
+// translation of the staged copies (the kernel is translation invariant; pass the same scan for targets and sources),
+// nullptr: none (FP64 only).
 // sort: stage a square operator's points in spatial order with culling boxes (MIXED only; see Staged).
 // parts (FP32): which copies its products will read, the direct kernels' coordinates or the block kernels' split rows.
 enum StageParts { kStageDirect = 1, kStageSplit = 2, kStageAll = 3 };

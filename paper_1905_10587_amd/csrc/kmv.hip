@@ -889,7 +889,7 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
     double bestc = 1e300;
     for (int64_t E : {256, 512, 1024, 2048, 3072, 4096, 6144, 8192, 12288, 16384}) {
       // (mixed: the super-tile decides which pairs are summed as rows only, in FP32, so it stays as it was; FP64 takes
-      // the small ones where 1024 leaves CUs idle, with a block's start counted as about 30000 pairs)
+      // the small ones where 1024 leaves CUs idle, with a block's start counted as 12000 pairs)
       if (E % rows || (prec != KRR_FP64 && E < 1024)) continue;
       const int64_t ns = ceil_div(T.npad, E);
       if ((double)ns * T.npad * 8.0 > 2.2e9 && E != 16384) continue;
@@ -904,8 +904,9 @@ void kmv_launch(const Staged& T, const Staged& S, StagedVec& V, int deriv, const
       bestE = split_req;
     const int64_t ns = ceil_div(T.npad, bestE);
     const int64_t items = ns * (ns + 1) / 2;
-    // Mixed: a super-tile may be shared by sub^2 blocks without another result.  The same cost, with a block's start
-    // and the pass over the partials (about 0.055 pairs a byte / 8) counted: below some 40000 points blocks are wanting.
+    // Mixed: a super-tile may be shared by sub^2 blocks: every FP32 sum keeps its terms, and the FP64 sums over them
+    // (24-bit values, so mostly exact) are grouped in more slots.  The same cost, with a block's start as 30000 pairs and
+    // the pass over the partials as 0.055 pairs a value: below some 40000 points blocks are wanting.
     int sub = 1;
     if (prec == KRR_MIXED) {
       auto cost = [&](int64_t b) {

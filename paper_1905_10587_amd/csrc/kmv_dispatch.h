@@ -42,8 +42,8 @@ bool with_coordinates(int d, F f) {
 }
 
 // FP64 / FP32 direct kernels: D in {2,3,4,6,8,16,32,64,128}, TM in {1,2,4} (D >= 32: TM 1),
-// RC in {1,4,8}, DV in {0,2}; FP64 with D > 32 has 64 targets to a block; FP64 also RC in {16, 32} with TM 1, DV 0, D <= 16.  Return false if the
-// combination is not instantiated.
+// RC in {1,4,8}, DV in {0,2}; FP64 with D > 32 has 64 targets to a block; FP64 also RC in {16, 32} with TM 1, DV 0, D <= 16.
+// Return false if the combination is not instantiated.
 bool launch_kmv_f64(int D, int TM, int RC, int DV, const KmvGrid& g, const double* xt, const double* xs,
                     const double* v, double neg_c, double* part, hipStream_t s);
 // Symmetric FP64 square product of one column (D in {2, 4, 6, 8, 16}, TM in {2, 4}).
@@ -54,7 +54,7 @@ bool launch_kmv_f64_sym(int D, int TM, const KmvGrid& g, const double* x, const 
 bool launch_kmv_f64_symm(int D, int NFR, bool clamp, const KmvGrid& g, const double* x, const double* v, double neg_c,
                          double* part, hipStream_t s);
 bool kmv_f64_has_sym(int D);
-// FP64 many-column product on the FP64 matrix cores: D <= 16 (instantiated D), NRG in {1, 2, 4, 8} groups
+// FP64 many-column product on the FP64 matrix cores: D <= 16 (instantiated D), NRG in {1, 2, 4, 6, 8} groups
 // of 16 columns per block (Rp a multiple of 16; the last block may be partly filled), K only.
 bool launch_kmv_f64_mfma(int D, int NRG, const KmvGrid& g, const double* xt, const double* xs, const double* v,
                          double neg_c, double* part, hipStream_t s);

@@ -16,7 +16,9 @@ static void go32(const KmvGrid& g, const float* xt, const float* xs, const float
     hipLaunchKernelGGL((k_kmv_f32<D, TM, RC, DV, DR>), g.grid, dim3(256), 0, s, xt, xs, v, g.Rp, g.src_len, g.n_src,
                        part, g.mpad, g.Rout);
   };
-  // (eight columns hide one coordinate of six or eight: 20011 points, d = 5, 7 columns 288 us with six, 304 with five)
+  // Chunks of eight columns keep the staged width of up to eight coordinates: a call of 4000, 20011 and 60000 points with 5
+  // to 8 columns takes 60, 264 and 1880 us over six coordinates and 67, 277 and 1906 over the real five, and 62, 284 and
+  // 2186 over eight against 62, 292 and 2297 over seven.  One coordinate of two is the other way by 1, 3 and 5%.
   if constexpr (TM == 1 && (RC < 8 || D > 8)) with_coordinates<D>(g.d, go);
   else go(std::integral_constant<int, D>{});
 }

@@ -4,7 +4,8 @@
 // Build, all on the device:
 //   sketch Y (Algorithm 1: K Omega^T through the kernel MVM; Algorithm 2: sparse sketch kernel)
 //   -> pivoted QR of Y^T -> anchors S (first k pivots)
-//   -> K_SS = U^{-1} -> EVD (one-sided Jacobi on its Cholesky factor) -> drop eigenvalues <= tau * max
+//   -> K_SS = U^{-1} -> EVD (one-sided Jacobi: FP64 handles on its Cholesky factor, others on K_SS itself)
+//   -> drop eigenvalues <= tau * max
 //   -> C = K(X, X_S) -> W = C V_kept diag(lam_kept)^{-1/2}  (so W W^T = C U C^T)
 //   -> M = W^T W (FP64) -> per beta: Cholesky L L^T = beta I + M (Eq. chol_factor), L^{-1},
 //      G = (beta I + M)^{-1} = L^{-T} L^{-1}.
