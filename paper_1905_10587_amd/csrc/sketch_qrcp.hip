@@ -494,13 +494,13 @@ __global__ __launch_bounds__(256) void k_qr_compact(const double* __restrict__ n
   }
 }
 
-// Sort keys: larger norm first, selected columns last (ascending order of the key).
+// Sort keys: larger norm first (ascending order of the key), last the selected columns and those whose norm is no number.
 __global__ void k_qr_keys(const double* __restrict__ nrm2, int64_t N, uint64_t* __restrict__ key,
                           int64_t* __restrict__ idx) {
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (c >= N) return;
   const double v = nrm2[c];
-  key[c] = v < 0.0 ? ~0ull : 0x7FFFFFFFFFFFFFFFull - (uint64_t)__double_as_longlong(v);
+  key[c] = v >= 0.0 ? 0x7FFFFFFFFFFFFFFFull - (uint64_t)__double_as_longlong(v) : ~0ull;
   idx[c] = c;
 }
 
@@ -595,7 +595,7 @@ __global__ __launch_bounds__(kQrCand / 2) void k_qr_pivots(const double* __restr
       const unsigned long long kk = bk[s & 1][w];
       if (wv > pv || (wv == pv && kk < pk)) { pv = wv; pk = kk; }
     }
-    if (pv < 0.0 || !(s == 0 || pv > tau)) break;   // (uniform)
+    if (!(pv >= 0.0) || !(s == 0 || pv > tau)) break;   // (uniform; no candidate, or none whose norm is a number: pk is none)
     const int p = (int)(pk & 0xffffffffu);
     double x0 = G[(int64_t)p * kQrCand + tid], x1 = G[(int64_t)p * kQrCand + tid + NT];
     const bool own0 = p == tid, own1 = p == tid + NT;
@@ -940,7 +940,7 @@ __global__ __launch_bounds__(256) void k_qr_refresh(const T* __restrict__ Yt, in
     __builtin_amdgcn_wave_barrier();
     const int64_t c = c0 + lane;
     double v = c < N ? nrm2[c] : -1.0;
-    if (v >= 0.0) {
+    if (!(v < 0.0)) {   // (a norm that is no number becomes 0, so that its column is picked after all others)
       for (int t = 0; t < b; ++t) {
         const double r = part[0][t][lane];
         v -= r * r;
